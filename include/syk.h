@@ -96,10 +96,11 @@ syk_status syk_apply_H(syk_terms t, syk_dtype dtype, int nvec, const int32_t* re
  * kernels and results as syk_apply_H (full space), with no hipMalloc, hipFree
  * or other allocation.  The buffers of the second, bit-rotated row layout
  * (psi copied in that layout and its partial output: 2 * min(nvec, 64) * dim
- * elements) come from a device scratch array of 128 MiB built into the library,
- * which each device the library runs on holds until the process ends (e.g.
- * N <= 44 in complex128 or N <= 46 in complex64 for one column; N < 30 needs
- * none).  Larger requests return SYK_EINVAL.  The handle's per-dtype tables and
+ * elements) and the partial sums of small states (at most 64 MiB, for products
+ * of fewer than 2^21 rows over all columns) come from a device scratch array of
+ * 128 MiB built into the library, which each device the library runs on holds
+ * until the process ends (e.g. N <= 44 in complex128 or N <= 46 in complex64
+ * for one column).  Larger requests return SYK_EINVAL.  The handle's per-dtype tables and
  * the diagonal of H are built by its first syk_apply_H call of that dtype and
  * block width: without one, SYK_EINVAL.  Every call on a device shares that
  * device's scratch, so calls that overlap in time on one device (other streams

@@ -9,7 +9,9 @@
 // from LDS, and each thread keeps its rows' sums in registers and writes them
 // once.
 //
-// Grid: (tiles, column groups); every workgroup serves NC consecutive columns
+// Grid: (tiles, column groups, parts); with fewer tiles and columns than the
+// chip holds workgroups, the chunks are split over `parts` workgroups per tile
+// and a second kernel adds their FP64 sums in order.  Every workgroup serves NC consecutive columns
 // of one realisation (NC = 1, or 2 for the two typical states a realisation
 // carries in a block), so mask records, PAIR weights and DIAG terms are
 // wave-uniform (scalar loads) and the chunk's QUAD tables are staged into LDS
@@ -50,6 +52,10 @@ struct KLayout {
     int col0;          // first column of this launch (column = col0 + NC blockIdx.y + c)
     uint32_t n_tiles;  // dim >> tile_bits
     int xcd_remap;     // spread consecutive tiles over XCDs in contiguous ranges
+    int n_parts;       // > 1: workgroup z sums only chunks part_chunk[z] .. part_chunk[z + 1] - 1 and its share of
+                       // the far masks, into its own slice of the FP64 partial sums
+    const uint32_t* __restrict__ part_chunk;
+    uint64_t part_stride;   // elements per slice: columns of the launch * dim
     int32_t real[kColsPerLaunch];  // realisation of each column of the launch
 };
 
@@ -144,11 +150,14 @@ __device__ __forceinline__ void cmac(R& pr, R& pi, R a, R b, const cplx<R>& v)
     pi = fma(b, v.re, pi);
 }
 
-template <typename R, int RPT, int NC>
+// SPLIT (the masks of a tile over several workgroups) is a template argument:
+// as run-time branches it cost the unsplit kernel 1% (N=52 complex128).
+template <typename R, int RPT, int NC, bool SPLIT>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(apply_waves(RPT, NC, sizeof(R)))))
 k_apply(KTerms<R> T, const QApplyChunk* __restrict__ chunks,
                                                const QRec* __restrict__ rec, KLayout L,
-                                               const cplx<R>* __restrict__ psi, cplx<R>* __restrict__ out)
+                                               const cplx<R>* __restrict__ psi, cplx<R>* __restrict__ out,
+                                               c128* __restrict__ parts)
 {
     constexpr int KB = ilog2c(RPT);
     constexpr uint32_t esz = sizeof(cplx<R>);
@@ -210,13 +219,20 @@ k_apply(KTerms<R> T, const QApplyChunk* __restrict__ chunks,
     // column c's source row at byte offset off of its tile
     auto src_row = [&](int c, uint32_t off) { return src_at(off + (uint32_t)c * TS * esz); };
 
-    for (int g = 0; g < L.n_chunks; ++g) {
+    int g0 = 0, g1 = L.n_chunks, f0 = 0, f1 = L.n_far;
+    if constexpr (SPLIT) {
+        g0 = (int)L.part_chunk[blockIdx.z];
+        g1 = (int)L.part_chunk[blockIdx.z + 1];
+        f0 = (int)((uint32_t)L.n_far * blockIdx.z / (uint32_t)L.n_parts);
+        f1 = (int)((uint32_t)L.n_far * (blockIdx.z + 1) / (uint32_t)L.n_parts);
+    }
+    for (int g = g0; g < g1; ++g) {
         const QApplyChunk C = chunks[g];
         uint32_t n_flat = 0;   // flat PAIR masks (no flipped k bit), first among the PAIR records
 #pragma unroll
         for (int b = 0; b < 8; ++b) n_flat += (C.pcnt[b >> 2] >> (8 * (b & 3))) & 0xffu;
         __syncthreads();   // previous chunk is done with src / tabs
-        if (C.new_tile) {
+        if (C.new_tile || (SPLIT && g == g0)) {
             const uint64_t sbase = (uint64_t)(tile ^ C.x_high) << L.tile_bits;
 #pragma unroll
             for (int c = 0; c < NC; ++c)
@@ -515,22 +531,22 @@ k_apply(KTerms<R> T, const QApplyChunk* __restrict__ chunks,
     // QUAD masks that flip only tile bits: D_x is one number per tile, the
     // source rows are the same rows of tile ^ x_high.  Streamed straight from
     // global memory with the next mask's rows loaded one mask ahead.
-    if (L.n_far > 0) {
+    if (f1 > f0) {
         cplx<R> vn[NC][RPT];
-        FarRec fn = L.far[0];
+        FarRec fn = L.far[f0];
         const cplx<R>* sp = psi + ((uint64_t)(tile ^ fn.x_high) << L.tile_bits);
 #pragma unroll
         for (int c = 0; c < NC; ++c)
 #pragma unroll
             for (int k = 0; k < RPT; ++k) vn[c][k] = (sp + c * L.dim)[tid + k * nt];
-        for (int f = 0; f < L.n_far; ++f) {
+        for (int f = f0; f < f1; ++f) {
             const FarRec fc = fn;
             cplx<R> v[NC][RPT];
 #pragma unroll
             for (int c = 0; c < NC; ++c)
 #pragma unroll
                 for (int k = 0; k < RPT; ++k) v[c][k] = vn[c][k];
-            if (f + 1 < L.n_far) {
+            if (f + 1 < f1) {
                 fn = L.far[f + 1];
                 sp = psi + ((uint64_t)(tile ^ fn.x_high) << L.tile_bits);
 #pragma unroll
@@ -549,6 +565,16 @@ k_apply(KTerms<R> T, const QApplyChunk* __restrict__ chunks,
         }
         if (kSplit) carry();
     }
+    if constexpr (SPLIT) {
+        parts += blockIdx.z * L.part_stride + (uint64_t)(blockIdx.y * NC) * L.dim + base + tid;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int k = 0; k < RPT; ++k)
+                parts[c * L.dim + k * nt] = kSplit ? c128{acc_re[c][k], acc_im[c][k]}
+                                                   : c128{(double)pr[c][k], (double)pi[c][k]};
+        return;
+    }
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -558,6 +584,42 @@ k_apply(KTerms<R> T, const QApplyChunk* __restrict__ chunks,
             o.im = kSplit ? (R)acc_im[c][k] : pi[c][k];
             (out + c * L.dim)[(uint64_t)base + tid + k * nt] = o;
         }
+}
+
+// out[e] = sum over p of parts[p * n + e], e < n: the slices of a launch with
+// its masks split over n_parts workgroups per tile.  A workgroup owns 32
+// elements and eight threads share one (slices p = s, s + 8, ...; the eight sums
+// are added in order through LDS), so that few rows with many slices still
+// keep enough loads in flight.  n is a multiple of 32 or the tail is masked.
+template <typename R>
+__global__ void __launch_bounds__(256) k_sum_parts(const c128* __restrict__ parts, int n_parts, uint64_t n,
+                                                   cplx<R>* __restrict__ out)
+{
+    __shared__ c128 red[8][32];
+    const uint32_t l = threadIdx.x & 31u, s = threadIdx.x >> 5;
+    const uint64_t e = (uint64_t)blockIdx.x * 32 + l;
+    c128 a{0.0, 0.0};
+    if (e < n) {
+#pragma unroll 4
+        for (int p = (int)s; p < n_parts; p += 8) {
+            const c128 v = parts[(uint64_t)p * n + e];
+            a.re += v.re;
+            a.im += v.im;
+        }
+    }
+    red[s][l] = a;
+    __syncthreads();
+    if (s == 0 && e < n) {
+#pragma unroll
+        for (int k = 1; k < 8; ++k) {
+            a.re += red[k][l].re;
+            a.im += red[k][l].im;
+        }
+        cplx<R> o;
+        o.re = (R)a.re;
+        o.im = (R)a.im;
+        out[e] = o;
+    }
 }
 
 // dst = transpose of src viewed as a [2^log_h] x [2^log_w] matrix (row-major),
@@ -640,40 +702,64 @@ void launch_transpose(syk_dtype dtype, const void* src, void* dst, int log_h, in
 
 namespace {
 
-template <typename R>
-void launch_t(const ApplyPlan& P, const KTerms<R>& T, const QApplyChunk* chunks, const QRec* rec, KLayout L,
-              int ncols, int nc, const void* psi, void* out, hipStream_t s)
+template <typename R, bool SPLIT>
+void launch_k_apply(const ApplyPlan& P, const KTerms<R>& T, const QApplyChunk* chunks, const QRec* rec,
+                    const KLayout& L, int ncols, int nc, const cplx<R>* in, cplx<R>* o, c128* parts, hipStream_t s)
 {
-    auto* in = static_cast<const cplx<R>*>(psi);
-    auto* o = static_cast<cplx<R>*>(out);
     if (nc == 2) {
         // the caller has checked that the columns pair up by realisation
         if (ncols % 2 != 0) throw Error(SYK_EINVAL, "apply_H: odd column count for two columns per workgroup");
-        dim3 grid(L.n_tiles, ncols / 2), block(P.nt);
+        dim3 grid(L.n_tiles, ncols / 2, L.n_parts), block(P.nt);
         switch (P.rpt) {
-        case 4: hipLaunchKernelGGL((k_apply<R, 4, 2>), grid, block, 0, s, T, chunks, rec, L, in, o); break;
-        case 8: hipLaunchKernelGGL((k_apply<R, 8, 2>), grid, block, 0, s, T, chunks, rec, L, in, o); break;
+        case 4: hipLaunchKernelGGL((k_apply<R, 4, 2, SPLIT>), grid, block, 0, s, T, chunks, rec, L, in, o, parts); break;
+        case 8: hipLaunchKernelGGL((k_apply<R, 8, 2, SPLIT>), grid, block, 0, s, T, chunks, rec, L, in, o, parts); break;
         default: throw Error(SYK_EINVAL, "apply_H: two columns per workgroup need 4 or 8 rows per thread");
         }
     } else {
-        dim3 grid(L.n_tiles, ncols), block(P.nt);
+        dim3 grid(L.n_tiles, ncols, L.n_parts), block(P.nt);
         switch (P.rpt) {
-        case 1: hipLaunchKernelGGL((k_apply<R, 1, 1>), grid, block, 0, s, T, chunks, rec, L, in, o); break;
-        case 2: hipLaunchKernelGGL((k_apply<R, 2, 1>), grid, block, 0, s, T, chunks, rec, L, in, o); break;
-        case 4: hipLaunchKernelGGL((k_apply<R, 4, 1>), grid, block, 0, s, T, chunks, rec, L, in, o); break;
-        case 8: hipLaunchKernelGGL((k_apply<R, 8, 1>), grid, block, 0, s, T, chunks, rec, L, in, o); break;
+        case 1: hipLaunchKernelGGL((k_apply<R, 1, 1, SPLIT>), grid, block, 0, s, T, chunks, rec, L, in, o, parts); break;
+        case 2: hipLaunchKernelGGL((k_apply<R, 2, 1, SPLIT>), grid, block, 0, s, T, chunks, rec, L, in, o, parts); break;
+        case 4: hipLaunchKernelGGL((k_apply<R, 4, 1, SPLIT>), grid, block, 0, s, T, chunks, rec, L, in, o, parts); break;
+        case 8: hipLaunchKernelGGL((k_apply<R, 8, 1, SPLIT>), grid, block, 0, s, T, chunks, rec, L, in, o, parts); break;
         default: throw Error(SYK_EINVAL, "apply_H: unsupported rows per thread");
         }
     }
     SYK_HIP(hipGetLastError());
 }
 
+template <typename R>
+void launch_t(const ApplyPlan& P, const KTerms<R>& T, const QApplyChunk* chunks, const QRec* rec, const KLayout& L,
+              int ncols, int nc, const void* psi, void* out, c128* parts, hipStream_t s)
+{
+    auto* in = static_cast<const cplx<R>*>(psi);
+    auto* o = static_cast<cplx<R>*>(out);
+    if (L.n_parts > 1) launch_k_apply<R, true>(P, T, chunks, rec, L, ncols, nc, in, o, parts, s);
+    else launch_k_apply<R, false>(P, T, chunks, rec, L, ncols, nc, in, o, parts, s);
+    if (L.n_parts > 1) {
+        const uint64_t n = L.part_stride;
+        hipLaunchKernelGGL(k_sum_parts<R>, dim3((uint32_t)((n + 31) / 32)), dim3(256), 0, s, parts, L.n_parts, n, o);
+        SYK_HIP(hipGetLastError());
+    }
+}
+
+constexpr int kSplitGroups = 1024, kMaxParts = 64;
+
+// About what a mask costs a workgroup, in single QUAD masks (a PAIR mask has
+// twice the arithmetic and reads its weights with scalar loads; one that flips
+// a k bit forms its coefficient row by row), and what a chunk's barriers and a
+// staged source tile cost.  Only used to cut the masks into parts of similar
+// cost.
+constexpr double kCostFlatPair = 5.0, kCostPair = 9.0, kCostDiag = 2.0, kCostChunk = 4.0, kCostTile = 8.0;
+
 // Chunks and class-sorted records of the apply kernel for tiles of 2^tile_bits
 // rows, 2^lane_bits threads and elements of esz bytes.  masks must be sorted by
 // x; QUAD masks that neither flip nor sign-depend on a row bit inside a tile go
-// to the far list.
+// to the far list.  max_cost > 0 ends a chunk before the cost of its masks
+// would pass it.
 void build_apply_tables(const std::vector<MaskRec>& masks_in, int tile_bits, int lane_bits, uint32_t esz,
-                        std::vector<QApplyChunk>& chunks, std::vector<QRec>& recs, std::vector<FarRec>& far)
+                        std::vector<QApplyChunk>& chunks, std::vector<QRec>& recs, std::vector<FarRec>& far,
+                        double max_cost = 0.0)
 {
     const uint32_t row_mask = (1u << tile_bits) - 1u;
     const uint32_t lane_mask = (1u << lane_bits) - 1u;
@@ -691,6 +777,9 @@ void build_apply_tables(const std::vector<MaskRec>& masks_in, int tile_bits, int
     auto zk_of = [&](const MaskRec& m) { return (int)((m.zbase >> lane_bits) & kbits_mask); };
     // table slots (16 entries each) a mask stages
     auto slots_of = [&](const MaskRec& m) { return type_of(m) == MASK_DIAG ? 0u : 1u; };
+    auto cost_of = [&](const MaskRec& m) {
+        return type_of(m) == MASK_QUAD ? 1.0 : type_of(m) == MASK_DIAG ? kCostDiag : flat_pair(m) ? kCostFlatPair : kCostPair;
+    };
     // Inside a run of one x_high: by lane flips, then by k flips, so that the
     // masks of a group are adjacent (a chunk boundary rarely splits one).
     std::vector<MaskRec> masks = masks_in;
@@ -709,6 +798,7 @@ void build_apply_tables(const std::vector<MaskRec>& masks_in, int tile_bits, int
         const uint32_t xh = masks[i].x >> tile_bits;
         const uint32_t cap = (uint32_t)apply_chunk_masks(esz);   // masks and table slots per chunk
         uint32_t used = 0;
+        double cost = 0.0;
         while (i < masks.size() && (masks[i].x >> tile_bits) == xh && mem.size() < cap) {
             const MaskRec& m = masks[i];
             // far: coefficient constant over a tile (no flipped qubit and no Z-string bit inside it)
@@ -716,7 +806,9 @@ void build_apply_tables(const std::vector<MaskRec>& masks_in, int tile_bits, int
                 far.push_back({m.x >> tile_bits, m.qpack, m.zbase, m.type_tab & 0x0fffffffu});
             } else {
                 if (used + slots_of(m) > cap) break;
+                if (max_cost > 0.0 && !mem.empty() && cost + cost_of(m) > max_cost) break;
                 used += slots_of(m);
+                cost += cost_of(m);
                 mem.push_back((uint32_t)i);
             }
             ++i;
@@ -854,6 +946,28 @@ void build_apply_tables(const std::vector<MaskRec>& masks_in, int tile_bits, int
     recs.push_back(QRec{});   // one record past the end: loads may run one ahead
 }
 
+// Chunk boundaries of n_parts contiguous parts of similar cost
+// (part_chunk[p] .. part_chunk[p + 1] - 1; parts may be empty).
+std::vector<uint32_t> part_bounds(const std::vector<QApplyChunk>& chunks, int n_parts)
+{
+    std::vector<double> sum(chunks.size() + 1, 0.0);
+    for (size_t g = 0; g < chunks.size(); ++g) {
+        const QApplyChunk& c = chunks[g];
+        uint32_t n_flat = 0;
+        for (int b = 0; b < 8; ++b) n_flat += (c.pcnt[b >> 2] >> (8 * (b & 3))) & 0xffu;
+        sum[g + 1] = sum[g] + c.n_quad + kCostFlatPair * n_flat + kCostPair * (c.n_pair - n_flat) + kCostDiag * c.n_diag +
+                     kCostChunk + (c.new_tile ? kCostTile : 0.0);
+    }
+    std::vector<uint32_t> b(n_parts + 1, (uint32_t)chunks.size());
+    uint32_t g = 0;
+    for (int p = 0; p < n_parts; ++p) {
+        // the first chunk whose middle lies at or after the part's start
+        while (g < chunks.size() && 0.5 * (sum[g] + sum[g + 1]) < sum.back() * p / n_parts) ++g;
+        b[p] = g;
+    }
+    return b;
+}
+
 // Bit rotation of the second layout: bits s..M-1 of a row become bits
 // 0..M-s-1 and bits 0..s-1 become the top bits.
 inline uint32_t rotate_bits(uint32_t v, int M, int s)
@@ -929,7 +1043,7 @@ namespace {
 
 int apply_tables_key(const ApplyPlan& P, uint32_t esz, int layout)
 {
-    return (((P.tile_bits * 16 + P.lb) * 32 + (int)esz) * 2 + P.two_layouts) * 2 + layout;
+    return ((((P.tile_bits * 16 + P.lb) * 32 + (int)esz) * 2 + P.two_layouts) * 2 + layout) * 256 + P.parts;
 }
 
 const HamiltonianDev::ApplyTables& apply_tables_for(const HamiltonianDev& H, const ApplyPlan& P, uint32_t esz,
@@ -942,7 +1056,10 @@ const HamiltonianDev::ApplyTables& apply_tables_for(const HamiltonianDev& H, con
         std::vector<QRec> rc;
         std::vector<FarRec> far;
         const std::vector<MaskRec> masks = layout_masks(*H.host_masks, H.M, P.tile_bits, P.two_layouts != 0, layout);
-        build_apply_tables(masks, P.tile_bits, P.lb, esz, ch, rc, far);
+        // parts of a split launch: chunks of at most half a part's share, so that the parts come out even
+        const double cost = (double)masks.size() + 4.0 * H.M * H.M / 2;
+        build_apply_tables(masks, P.tile_bits, P.lb, esz, ch, rc, far,
+                           P.parts > 1 ? std::max(6.0, 0.5 * cost / P.parts) : 0.0);
         std::unique_ptr<HamiltonianDev::ApplyTables> t(new HamiltonianDev::ApplyTables());
         t->n_chunks = (int)ch.size();
         t->n_far = (int)far.size();
@@ -953,6 +1070,11 @@ const HamiltonianDev::ApplyTables& apply_tables_for(const HamiltonianDev& H, con
         if (!far.empty()) {
             t->far.ensure(far.size() * sizeof(FarRec));
             SYK_HIP(hipMemcpy(t->far.p, far.data(), far.size() * sizeof(FarRec), hipMemcpyHostToDevice));
+        }
+        if (P.parts > 1) {
+            const std::vector<uint32_t> pb = part_bounds(ch, P.parts);
+            t->part_chunk.ensure(pb.size() * sizeof(uint32_t));
+            SYK_HIP(hipMemcpy(t->part_chunk.p, pb.data(), pb.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
         }
         t->recs.ensure(rc.size() * sizeof(QRec));
         SYK_HIP(hipMemcpy(t->recs.p, rc.data(), rc.size() * sizeof(QRec), hipMemcpyHostToDevice));
@@ -967,11 +1089,24 @@ ApplyPlan plan_apply(int M, int nvec, syk_dtype dtype, const ApplyTuning* tune)
 {
     ApplyPlan P{};
     P.slices = (nvec + kColsPerLaunch - 1) / kColsPerLaunch;
-    // 2048-row source tiles (256 threads, 8 rows each); smaller tiles when the
-    // columns would not fill the chip.
+    // 2048-row source tiles (256 threads, 8 rows each).  Where the tiles and
+    // columns of a launch are fewer than kSplitGroups (four workgroups on each
+    // of the 256 CUs), the masks are split over several workgroups per tile:
+    // up to there the full tile's arithmetic per mask is worth more than the
+    // partial sums cost (16 B written and read per row and part).  One column,
+    // complex128, us per call, smaller tiles without a split (before) -> split:
+    // N=24 127 -> 16, N=32 383 -> 62, N=36 771 -> 261, N=40 2450 -> 1400; half
+    // or twice the number of workgroups: N=32 67 / 70, N=40 1705 / 1351.  More
+    // than 64 parts leave too few masks each (N=28: 28.0 with 64, 32.1 with 128).
+    // A shape given by the caller is run as it is given, unsplit.
     int tb = std::min(M, 11);
-    while (tb > 8 && ((int64_t)1 << (M - tb)) * nvec < 2048) --tb;
-    if (tune && tune->tile_bits > 0) tb = std::min(tune->tile_bits, M);
+    P.parts = 1;
+    if (tune && tune->tile_bits > 0) {
+        tb = std::min(tune->tile_bits, M);
+    } else {
+        const int64_t wg = ((int64_t)1 << (M - tb)) * std::min(nvec, kColsPerLaunch);
+        if (wg < kSplitGroups) P.parts = (int)std::min<int64_t>(kMaxParts, (kSplitGroups + wg - 1) / wg);
+    }
     // 8 lane bits; a thread owns 2^(tile_bits - 8) rows, at most 8
     if (tb > kLaneBits + kMaxKBits) throw Error(SYK_EINVAL, "apply_H: tile_bits above 11");
     P.tile_bits = tb;
@@ -993,16 +1128,25 @@ ApplyPlan plan_apply(int M, int nvec, syk_dtype dtype, const ApplyTuning* tune)
     }
     // QUAD masks whose four qubits all lie above the tile would each stream a
     // whole tile from global memory; with at least C(7,4) of them, run the
-    // masks that sit better in the rotated layout there.
-    P.two_layouts = (M - tb >= 7 && tb >= 8) ? 1 : 0;
+    // masks that sit better in the rotated layout there.  A split launch is
+    // short enough that the second layout's launches (two transposes, another
+    // product and sum) weigh more: from C(8,4) on (N=36: 261 us with one layout,
+    // 283 with two; N=38: 583 both; N=34, where C(6,4): 120 with one, 146 with two).
+    P.two_layouts = (M - tb >= (P.parts > 1 ? 8 : 7) && tb >= 8) ? 1 : 0;
     return P;
 }
 
 namespace {
 void launch_apply_impl(const HamiltonianDev& H, syk_dtype dtype, int nvec, const int32_t* real_of_col,
                        const void* psi, void* out, const ApplyPlan& P, hipStream_t s, void* rot_in, void* rot_out,
-                       bool timed);
+                       void* parts, bool timed);
 }  // namespace
+
+// Bytes of the partial sums of a split launch (FP64 for both state types).
+static size_t parts_bytes(const ApplyPlan& P, int nvec, uint64_t dim)
+{
+    return P.parts > 1 ? (size_t)P.parts * std::min(nvec, kColsPerLaunch) * dim * sizeof(c128) : 0;
+}
 
 // Scratch of the allocation-free apply (syk_apply_H_noalloc): the rotated
 // copy of psi and the rotated layout's output of one call, side by side.  Each
@@ -1034,8 +1178,9 @@ void launch_apply_h_noalloc(const HamiltonianDev& H, int device, syk_dtype dtype
     const size_t esz = elem_bytes(dtype);
     const uint64_t dim = (uint64_t)1 << H.M;
     const size_t half = (size_t)std::min(nvec, kColsPerLaunch) * dim * esz;
-    if (P.two_layouts && 2 * half > kNoAllocScratchBytes)
-        throw Error(SYK_EINVAL, "apply_H_noalloc: the rotated layout needs " + std::to_string(2 * half) +
+    const size_t rot = P.two_layouts ? 2 * half : 0, part = parts_bytes(P, nvec, dim);
+    if (rot + part > kNoAllocScratchBytes)
+        throw Error(SYK_EINVAL, "apply_H_noalloc: the call needs " + std::to_string(rot + part) +
                                     " bytes of scratch, above the maximum of " +
                                     std::to_string(kNoAllocScratchBytes));
     // everything the handle builds on first use must exist already
@@ -1043,8 +1188,9 @@ void launch_apply_h_noalloc(const HamiltonianDev& H, int device, syk_dtype dtype
     if (!H.diag_ready || !have(0) || (P.two_layouts && !have(1)))
         throw Error(SYK_EINVAL, "apply_H_noalloc: the handle has no tables for this dtype and block width yet "
                                 "(call syk_apply_H once with them first)");
-    char* sp = P.two_layouts ? static_cast<char*>(noalloc_scratch_ptr(device)) : nullptr;
-    launch_apply_impl(H, dtype, nvec, real_of_col, psi, out, P, s, sp, sp ? sp + half : nullptr, false);
+    char* sp = rot + part > 0 ? static_cast<char*>(noalloc_scratch_ptr(device)) : nullptr;
+    launch_apply_impl(H, dtype, nvec, real_of_col, psi, out, P, s, rot ? sp : nullptr, rot ? sp + half : nullptr,
+                      part ? sp + rot : nullptr, false);
 }
 
 void launch_apply_h(const HamiltonianDev& H, syk_dtype dtype, int nvec, const int32_t* real_of_col,
@@ -1056,9 +1202,10 @@ void launch_apply_h(const HamiltonianDev& H, syk_dtype dtype, int nvec, const in
         H.rot_in.ensure(bytes);
         H.rot_out.ensure(bytes);
     }
+    if (P.parts > 1) H.parts.ensure(parts_bytes(P, nvec, (uint64_t)1 << H.M));
     ensure_diag(H, s);
     launch_apply_impl(H, dtype, nvec, real_of_col, psi, out, P, s, two ? H.rot_in.p : nullptr,
-                      two ? H.rot_out.p : nullptr, true);
+                      two ? H.rot_out.p : nullptr, P.parts > 1 ? H.parts.p : nullptr, true);
 }
 
 namespace {
@@ -1067,7 +1214,7 @@ namespace {
 // min(nvec, 64) columns for two-layout plans.  Allocates nothing.
 void launch_apply_impl(const HamiltonianDev& H, syk_dtype dtype, int nvec, const int32_t* real_of_col,
                        const void* psi, void* out, const ApplyPlan& P, hipStream_t s, void* rot_in, void* rot_out,
-                       bool timed)
+                       void* parts, bool timed)
 {
     const int M = H.M;
     if (P.lb > kLaneBits || (P.rpt > 1 && P.lb != kLaneBits) || P.nt != (1 << P.lb) ||
@@ -1080,6 +1227,7 @@ void launch_apply_impl(const HamiltonianDev& H, syk_dtype dtype, int nvec, const
     const HamiltonianDev::ApplyTables& A = apply_tables_for(H, P, (uint32_t)esz, 0);
     const HamiltonianDev::ApplyTables* B = P.two_layouts ? &apply_tables_for(H, P, (uint32_t)esz, 1) : nullptr;
     if (B && (!rot_in || !rot_out)) throw Error(SYK_EINVAL, "apply_H: no buffers for the rotated layout");
+    if (P.parts > 1 && !parts) throw Error(SYK_EINVAL, "apply_H: no buffer for the partial sums");
     if (timed) timing_begin(s);
     for (int sl = 0; sl < P.slices; ++sl) {
         KLayout L{};
@@ -1103,14 +1251,17 @@ void launch_apply_impl(const HamiltonianDev& H, syk_dtype dtype, int nvec, const
             L.far = Tb.far.as<FarRec>();
             L.n_far = Tb.n_far;
             L.n_chunks = Tb.n_chunks;
+            L.n_parts = P.parts;
+            L.part_chunk = Tb.part_chunk.as<uint32_t>();
+            L.part_stride = (uint64_t)ncols * dim;
             const auto* ch = Tb.chunks.as<QApplyChunk>();
             const auto* rc = Tb.recs.as<QRec>();
             if (dtype == SYK_C128) {
                 KTerms<double> T{H.tab4_d, H.qinfo, H.phi2_d, H.w2_d, H.diag.as<double>(), H.n_real, M};
-                launch_t<double>(P, T, ch, rc, L, ncols, nc, src, dst, s);
+                launch_t<double>(P, T, ch, rc, L, ncols, nc, src, dst, static_cast<c128*>(parts), s);
             } else {
                 KTerms<float> T{H.tab4_f, H.qinfo, H.phi2_f, H.w2_f, H.diag.as<double>(), H.n_real, M};
-                launch_t<float>(P, T, ch, rc, L, ncols, nc, src, dst, s);
+                launch_t<float>(P, T, ch, rc, L, ncols, nc, src, dst, static_cast<c128*>(parts), s);
             }
         };
         if (B) {

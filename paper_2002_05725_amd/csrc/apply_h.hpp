@@ -72,6 +72,7 @@ struct ApplyPlan {
     int rpt;         // tile rows per thread
     int xcd_remap;
     int two_layouts; // also run the masks that flip few rows of a tile on a bit-rotated copy
+    int parts;       // > 1: the masks are split over this many workgroups per tile, whose sums a second kernel adds
     int nc;          // columns per workgroup where a launch's columns pair up by realisation (1 or 2)
 };
 
@@ -112,8 +113,8 @@ void launch_apply_h(const HamiltonianDev& H, syk_dtype dtype, int nvec, const in
 // Bytes of the file-scope device scratch of the allocation-free apply.
 constexpr size_t kNoAllocScratchBytes = (size_t)128 << 20;
 
-// launch_apply_h without any allocation: the rotated layout's two buffers come
-// from the scratch array of `device` (the current device), and the handle's
+// launch_apply_h without any allocation: the rotated layout's two buffers and a
+// split launch's partial sums come from the scratch array of `device` (the current device), and the handle's
 // tables for this launch shape and its diagonal must exist already (SYK_EINVAL
 // otherwise, as for plans whose buffers exceed kNoAllocScratchBytes).  Calls
 // that overlap on one device race on the scratch.

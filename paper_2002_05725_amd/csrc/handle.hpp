@@ -29,12 +29,14 @@ struct HamiltonianDev {
     const std::vector<uint64_t>* bin_off = nullptr;
     // Per-launch-shape chunks and class-sorted records of the apply kernel.
     struct ApplyTables {
-        DevBuf chunks, recs, far;
+        DevBuf chunks, recs, far, part_chunk;
         int n_chunks = 0, n_far = 0;
     };
     mutable std::map<int, std::unique_ptr<ApplyTables>> apply_tables;
     // Rotated copies of psi and of the second layout's output (two-layout plans).
     mutable DevBuf rot_in, rot_out;
+    // Partial sums of launches with their masks split over several workgroups per tile.
+    mutable DevBuf parts;
     // The diagonal of H per realisation (FP64, [n_real][2^M]), filled on the
     // first apply: it does not depend on the state.
     mutable DevBuf diag;
