@@ -77,4 +77,37 @@ struct DevBuf {
     T* as() const { return static_cast<T*>(p); }
 };
 
+// Pinned host buffer owned by the library, read by the host after the stream
+// that wrote it is synchronised.
+struct PinnedBuf {
+    void* p = nullptr;
+    size_t bytes = 0;
+    PinnedBuf() = default;
+    PinnedBuf(const PinnedBuf&) = delete;
+    PinnedBuf& operator=(const PinnedBuf&) = delete;
+    ~PinnedBuf() { release(); }
+    void release()
+    {
+        if (p) {
+            (void)hipDeviceSynchronize();   // work enqueued earlier may still write it
+            (void)hipHostFree(p);
+        }
+        p = nullptr;
+        bytes = 0;
+    }
+    void* get(size_t n)
+    {
+        if (n <= bytes) return p;
+        release();
+        n = n < 16384 ? 16384 : n;
+        hipError_t e = hipHostMalloc(&p, n, hipHostMallocDefault);
+        if (e != hipSuccess) {
+            p = nullptr;
+            throw Error(SYK_ENOMEM, std::string("hipHostMalloc of ") + std::to_string(n) + " bytes: " + hipGetErrorString(e));
+        }
+        bytes = n;
+        return p;
+    }
+};
+
 }  // namespace syk

@@ -4,10 +4,12 @@
 // is orthogonalised against all previous vectors with two passes of classical
 // Gram-Schmidt; inner products are FP64 on the device, T (tridiagonal QR for
 // its eigen-decomposition) and its exponential are FP64 on the host.  Up to 16 basis vectors the first pass's update and
-// the second pass's projection share one sweep over the basis.  The
+// the second pass's projection share one sweep over the basis (states of at
+// most 2048 rows do the whole iteration after the product in one launch).  The
 // projections, alpha, beta and the invariant-subspace test stay on the device
-// for the whole build (no host round trip per iteration); the host reads them
-// once at the end.
+// for the whole build (no host round trip per iteration); the last iteration
+// writes them to pinned host memory, which the host reads after one
+// synchronisation.
 #include "krylov.hpp"
 #include "tridiag_eig.hpp"
 
@@ -52,59 +54,19 @@ LanczosBasis lanczos_build(BlockCtx& c, const void* psi, int m)
     void* w = c.h.ws.get("krylov_w", vb);
     char* V = L.V;
 
-    std::vector<double> nrm2 = ops.norm2(psi);
-    L.nrm.assign(B, 0.0);
-    std::vector<double> inv(B);
-    for (int b = 0; b < B; ++b) {
-        if (!std::isfinite(nrm2[b])) throw Error(SYK_EBREAKDOWN, "non-finite norm in Krylov step");
-        L.nrm[b] = std::sqrt(nrm2[b]);
-        inv[b] = L.nrm[b] > 0 ? 1.0 / L.nrm[b] : 0.0;
-    }
-    ops.scale(V, psi, inv);
-
-    L.alpha.assign((size_t)m * B, 0.0);
-    L.beta.assign((size_t)m * B, 0.0);
-    L.kdim.assign(B, m);
-    // Device scalars: alpha, beta [m][B], then scale, nrm, f [B]; kdim [B] and
-    // the error flag.  A column whose subspace became invariant keeps f = 0,
-    // so its later basis vectors are zero.
-    const size_t nB = (size_t)B;
-    double* dd = (double*)c.h.ws.get("lz_dbl", (2 * (size_t)m + 3) * nB * sizeof(double));
-    int* di = (int*)c.h.ws.get("lz_int", (nB + 1) * sizeof(int));
-    {
-        std::vector<double> h((2 * (size_t)m + 3) * nB, 0.0);
-        std::copy(L.nrm.begin(), L.nrm.end(), h.begin() + (2 * (size_t)m + 1) * nB);
-        ops.to_device(dd, h.data(), h.size() * sizeof(double));
-        std::vector<int> hi(nB + 1, m);
-        hi[nB] = 0;
-        ops.to_device(di, hi.data(), hi.size() * sizeof(int));
-    }
-    LanczosScalars z{dd, dd + (size_t)m * nB, di, dd + 2 * (size_t)m * nB, dd + (2 * (size_t)m + 1) * nB,
-                     dd + (2 * (size_t)m + 2) * nB, di + nB};
-    // projections of up to m basis vectors (sized once: no reallocation inside the loop)
-    const size_t proj_bytes = (size_t)std::max(m, VecOps::kFusedMax) * nB * 2 * sizeof(double);
-    c.h.ws.get("gs_c1", proj_bytes);
-    c.h.ws.get("gs_c2", proj_bytes);
+    const LanczosScalars z = ops.lanczos_begin(psi, V, m);
     for (int j = 0; j < m; ++j) {
         c.apply_H(V + (size_t)j * vb, w);
-        const double* d1 = ops.multidot_dev(V, j + 1, w, "gs_c1");
-        const double* d2;
-        if (j + 1 <= VecOps::kFusedMax) {
-            d2 = ops.update_dot(w, V, j + 1, d1, "gs_c2");
-        } else {
-            ops.update_dev_norm(w, V, j + 1, d1, false);
-            d2 = ops.multidot_dev(V, j + 1, w, "gs_c2");
-        }
-        const double* wn = ops.update_dev_norm(w, V, j + 1, d2, true);
-        ops.lanczos_coef(d1, d2, wn, j, m, z);
-        if (j < m - 1) ops.scale_dev(V + (size_t)(j + 1) * vb, w, z.f);
+        ops.lanczos_step(w, V, j, m, z);
     }
-    ops.to_host(L.alpha.data(), z.alpha, L.alpha.size() * sizeof(double));
-    ops.to_host(L.beta.data(), z.beta, L.beta.size() * sizeof(double));
-    std::vector<int> hi(nB + 1);
-    ops.to_host(hi.data(), di, hi.size() * sizeof(int));
-    if (hi[nB] != 0) throw Error(SYK_EBREAKDOWN, "non-finite Lanczos coefficient");
-    std::copy(hi.begin(), hi.begin() + nB, L.kdim.begin());
+    ops.synchronize();
+    const size_t nB = (size_t)B;
+    L.alpha.assign(z.h_alpha, z.h_alpha + m * nB);
+    L.beta.assign(z.h_beta, z.h_beta + m * nB);
+    L.nrm.assign(z.h_nrm, z.h_nrm + nB);
+    L.kdim.assign(z.h_kdim, z.h_kdim + nB);
+    for (int b = 0; b < B; ++b)
+        if (z.h_flag[b] != 0) throw Error(SYK_EBREAKDOWN, "non-finite norm or Lanczos coefficient in Krylov step");
     return L;
 }
 

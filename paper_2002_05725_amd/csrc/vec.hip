@@ -138,7 +138,32 @@ void with_count(int k, F&& f)
     }
 }
 
-// partial[bx][k][c] = sum over this workgroup's rows of conj(V_k[r,c]) w[r,c]
+// Partial sums of a reduction of N doubles per column: [column][workgroup g < G][N].
+// Every workgroup of the kernel that uses the sums adds the G entries itself, in
+// a fixed order (256 / N strided groups, then the groups in order), or, for
+// large blocks, a finishing kernel has reduced them and G is 1 (kFusedRows).  The
+// result is in out[0..N) of LDS for every thread.
+template <int N>
+__device__ __forceinline__ void sum_partials(const double* __restrict__ partial, int G, double (&tmp)[RB],
+                                             double (&out)[N])
+{
+    constexpr int kGroups = RB / N;
+    const double* p = partial + (int64_t)blockIdx.y * G * N;
+    const int t = threadIdx.x, i = t % N, q = t / N;
+    double s = 0.0;
+    if (q < kGroups)
+        for (int g = q; g < G; g += kGroups) s += p[(int64_t)g * N + i];
+    tmp[t] = s;
+    __syncthreads();
+    if (t < N) {
+        double o = tmp[t];
+        for (int k = 1; k < kGroups; ++k) o += tmp[k * N + t];
+        out[t] = o;
+    }
+    __syncthreads();
+}
+
+// partial[c][bx][2k, 2k + 1] = sum over this workgroup's rows of conj(V_k[r,c]) w[r,c]
 template <typename R, int K>
 __global__ void __launch_bounds__(RB) k_multidot(const cplx<R>* __restrict__ V, int64_t vstride,
                                                  const cplx<R>* __restrict__ w, Shape S,
@@ -167,23 +192,25 @@ __global__ void __launch_bounds__(RB) k_multidot(const cplx<R>* __restrict__ V, 
     const double t = block_sum(a, 2 * K, red);
     // thread i < 2K holds (k, re/im) = (i / 2, i % 2)
     if ((int)threadIdx.x < 2 * K)
-        partial[(((int64_t)blockIdx.x * K + (threadIdx.x >> 1)) * S.B + blockIdx.y) * 2 + (threadIdx.x & 1)] = t;
+        partial[((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * (2 * K) + threadIdx.x] = t;
 }
 
-// w -= sum_k coef[k][c] V_k; optionally partial[bx][c] = sum |w_new|^2
+// w -= sum_k c_k V_k with c the sums of proj (G partial sums per column);
+// optionally partial[c][bx] = sum |w_new|^2
 template <typename R, int K>
 __global__ void __launch_bounds__(RB) k_update(cplx<R>* __restrict__ w, const cplx<R>* __restrict__ V,
-                                               int64_t vstride, const double* __restrict__ coef,
+                                               int64_t vstride, const double* __restrict__ proj, int G,
                                                Shape S, double* __restrict__ partial)
 {
-    __shared__ double red[kWaves];
+    __shared__ double tmp[RB], cs[2 * K];
     const int c = blockIdx.y;
     const int64_t col = (int64_t)c * S.D;
+    sum_partials<2 * K>(proj, G, tmp, cs);
     double cr[K], ci[K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        cr[k] = coef[(k * S.B + c) * 2];
-        ci[k] = coef[(k * S.B + c) * 2 + 1];
+        cr[k] = cs[2 * k];
+        ci[k] = cs[2 * k + 1];
     }
     double nrm = 0.0;
     const int64_t step = (int64_t)gridDim.x * RB;
@@ -208,27 +235,29 @@ __global__ void __launch_bounds__(RB) k_update(cplx<R>* __restrict__ w, const cp
     }
     if (!partial) return;
     double a[1] = {nrm};
-    const double t = block_sum(a, 1, red);
-    if (threadIdx.x == 0) partial[(int64_t)blockIdx.x * S.B + c] = t;
+    const double t = block_sum(a, 1, tmp);
+    if (threadIdx.x == 0) partial[(int64_t)c * gridDim.x + blockIdx.x] = t;
 }
 
 // The first Gram-Schmidt update fused with the second projection, for K
-// basis vectors: w' = w - sum_k coef[k][c] V_k (rounded to the state's
-// precision, as stored), and partial[bx][k][c] = sum over this workgroup's rows
-// of conj(V_k[r,c]) w'[r,c].  Each V_k[r] is read once for both uses.
+// basis vectors: w' = w - sum_k c_k V_k with c the sums of proj (w' rounded to
+// the state's precision, as stored), and partial[c][bx][k] = sum over this
+// workgroup's rows of conj(V_k[r,c]) w'[r,c].  Each V_k[r] is read once for both
+// uses.
 template <typename R, int K>
 __global__ void __launch_bounds__(RB) k_update_dot(cplx<R>* __restrict__ w, const cplx<R>* __restrict__ V,
-                                                   int64_t vstride, const double* __restrict__ coef,
+                                                   int64_t vstride, const double* __restrict__ proj, int G,
                                                    Shape S, double* __restrict__ partial)
 {
-    __shared__ double red[kWaves * 2 * K];
+    __shared__ double tmp[RB], cs[2 * K], red[kWaves * 2 * K];
     const int c = blockIdx.y;
     const int64_t col = (int64_t)c * S.D;
+    sum_partials<2 * K>(proj, G, tmp, cs);
     double cr[K], ci[K], a[2 * K];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        cr[k] = coef[(k * S.B + c) * 2];
-        ci[k] = coef[(k * S.B + c) * 2 + 1];
+        cr[k] = cs[2 * k];
+        ci[k] = cs[2 * k + 1];
         a[2 * k] = a[2 * k + 1] = 0.0;
     }
     const int64_t step = (int64_t)gridDim.x * RB;
@@ -257,86 +286,247 @@ __global__ void __launch_bounds__(RB) k_update_dot(cplx<R>* __restrict__ w, cons
         }
     }
     const double t = block_sum(a, 2 * K, red);
-    if ((int)threadIdx.x < 2 * K)
-        partial[(((int64_t)blockIdx.x * K + (threadIdx.x >> 1)) * S.B + c) * 2 + (threadIdx.x & 1)] = t;
+    if ((int)threadIdx.x < 2 * K) partial[((int64_t)c * gridDim.x + blockIdx.x) * (2 * K) + threadIdx.x] = t;
 }
 
-// The scalars of Lanczos iteration j for column b = thread: alpha_j =
-// Re(c1[j] + c2[j]) (the two projections on the newest basis vector), beta_j =
-// ||w||.  While the column is still growing its basis, its scale estimate
-// max_i (|alpha_i| + beta_{i-1}) is updated, and unless j is the last
-// iteration, beta_j at or below 1e-13 times that scale (or a zero start
-// vector) marks the subspace invariant (kdim = j + 1, f = 0); otherwise
-// f = 1 / beta_j scales w into the next basis vector.  A non-finite alpha or
-// beta sets flag[0].
-__global__ void k_lanczos_coef(const double* __restrict__ c1, const double* __restrict__ c2,
-                               const double* __restrict__ wnorm2, int j, int m, int B, double* __restrict__ alpha,
-                               double* __restrict__ beta, int* __restrict__ kdim, double* __restrict__ scale,
-                               const double* __restrict__ nrm, double* __restrict__ f, int* __restrict__ flag)
-{
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    const double a = c1[((size_t)j * B + b) * 2] + c2[((size_t)j * B + b) * 2];
-    const double bt = sqrt(wnorm2[b]);
-    if (!isfinite(a) || !isfinite(bt)) flag[0] = 1;
-    alpha[(size_t)j * B + b] = a;
-    beta[(size_t)j * B + b] = bt;
-    double fb = 0.0;
-    if (j < kdim[b]) {
-        scale[b] = fmax(scale[b], fabs(a) + (j > 0 ? beta[(size_t)(j - 1) * B + b] : 0.0));
-        if (j < m - 1) {
-            if (bt <= 1e-13 * scale[b] || nrm[b] == 0.0) kdim[b] = j + 1;
-            else fb = 1.0 / bt;
-        }
-    }
-    f[b] = fb;
-}
-
-// out[i] = sum of partial[g][i] over g < G, for i < n doubles: one wave per
-// output, lane l adding g = l, l + 64, ... in order, then a fixed butterfly
+// out[c][i] = sum of partial[c][g][i] over g < G, for i < n doubles: one wave
+// per output, lane l adding g = l, l + 64, ... in order, then a fixed butterfly
 // over the lanes (the same order on every run).
 __global__ void __launch_bounds__(64) k_finish(const double* __restrict__ partial, int G, int n,
                                                double* __restrict__ out)
 {
     const int i = blockIdx.x;
-    if (i >= n) return;
+    const int64_t c = blockIdx.y;
     double s = 0.0;
-    for (int g = (int)threadIdx.x; g < G; g += 64) s += partial[(int64_t)g * n + i];
+    for (int g = (int)threadIdx.x; g < G; g += 64) s += partial[(c * G + g) * n + i];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (threadIdx.x == 0) out[i] = s;
+    if (threadIdx.x == 0) out[c * n + i] = s;
 }
 
-void launch_finish(const double* partial, int G, int n, double* out, hipStream_t st)
+// The scalars of one column at Lanczos iteration j, the same on every thread
+// that calls it: alpha_j = a (the two projections on the newest basis vector),
+// beta_j = sqrt(wn).  While the column is still growing its basis, its scale
+// estimate max_i (|alpha_i| + beta_{i-1}) is updated, and unless j is the last
+// iteration, beta_j at or below 1e-13 times that scale (or a zero start vector)
+// marks the subspace invariant (kdim = j + 1, factor 0); otherwise the factor
+// 1 / beta_j scales w into the next basis vector.  Iteration j's scale and kdim
+// are read from slot j and written to slot j + 1, so that every workgroup of the
+// launch that forms the scalars reads the same values; one thread per column
+// (`writer`) stores.
+__device__ __forceinline__ double lanczos_scalars(const LanczosScalars& z, double a, double wn, int j, int m, int B,
+                                                  int c, bool writer)
 {
-    hipLaunchKernelGGL(k_finish, dim3(n), dim3(64), 0, st, partial, G, n, out);
-    SYK_HIP(hipGetLastError());
+    const double bt = sqrt(wn);
+    const size_t o = (size_t)j * B + c;
+    double sc = z.scale[o], f = 0.0;
+    int kd = z.kdim[o];
+    if (j < kd) {
+        sc = fmax(sc, fabs(a) + (j > 0 ? z.beta[o - B] : 0.0));
+        if (j < m - 1) {
+            if (bt <= 1e-13 * sc || z.nrm[c] == 0.0) kd = j + 1;
+            else f = 1.0 / bt;
+        }
+    }
+    if (writer) {
+        z.alpha[o] = a;
+        z.beta[o] = bt;
+        z.scale[o + B] = sc;
+        z.kdim[o + B] = kd;
+        if (!isfinite(a) || !isfinite(bt)) z.flag[c] = 1;
+    }
+    return f;
 }
 
-template <typename R>
-__global__ void __launch_bounds__(RB) k_scale(cplx<R>* out, const cplx<R>* in, const double* __restrict__ f, Shape S)
+// The scalars of one column start from its norm: slot 0, the error flag for a
+// norm that is not finite; returns 1 / norm (0 for a zero column).
+__device__ __forceinline__ double lanczos_start(const LanczosScalars& z, double n2, int m, int c, bool writer)
 {
-    const int64_t col = (int64_t)blockIdx.y * S.D;
-    const double fc = f[blockIdx.y];
-    const int64_t step = (int64_t)gridDim.x * RB;
-    for (int64_t r = (int64_t)blockIdx.x * RB + threadIdx.x; r < S.D; r += step) {
-        const int64_t e = col + r;
-        const cplx<R> v = in[e];
-        cplx<R> o;
-        o.re = (R)(fc * (double)v.re);
-        o.im = (R)(fc * (double)v.im);
-        out[e] = o;
+    const double nrm = sqrt(n2);
+    if (writer) {
+        z.nrm[c] = nrm;
+        z.scale[c] = 0.0;
+        z.kdim[c] = m;
+        z.flag[c] = isfinite(n2) ? 0 : 1;
+    }
+    return nrm > 0.0 ? 1.0 / nrm : 0.0;
+}
+
+// A column's results to the host mirror (pinned memory the host reads after
+// synchronising the stream: no copy in between).  One thread per iteration.
+__device__ __forceinline__ void lanczos_publish(const LanczosScalars& z, int m, int B, int c, int t, int nt)
+{
+    for (int k = t; k < m; k += nt) {
+        z.h_alpha[(size_t)k * B + c] = z.alpha[(size_t)k * B + c];
+        z.h_beta[(size_t)k * B + c] = z.beta[(size_t)k * B + c];
+    }
+    if (t == 0) {
+        z.h_nrm[c] = z.nrm[c];
+        z.h_kdim[c] = z.kdim[(size_t)m * B + c];
+        z.h_flag[c] = z.flag[c];
     }
 }
 
-// y = sum_k coef[k][c] V_k for all K vectors
+// V_0 = psi / ||psi|| and the scalars' start, from the G partial sums of ||psi||^2.
 template <typename R>
-__global__ void __launch_bounds__(RB) k_combine(cplx<R>* __restrict__ y, const cplx<R>* __restrict__ V,
-                                                int64_t vstride, int K, const double* __restrict__ coef, Shape S)
+__global__ void __launch_bounds__(RB) k_lanczos_start(const cplx<R>* __restrict__ psi, cplx<R>* __restrict__ V,
+                                                      const double* __restrict__ norm, int G, int m, Shape S,
+                                                      LanczosScalars z)
+{
+    __shared__ double tmp[RB], n2[2];
+    const int c = blockIdx.y;
+    sum_partials<2>(norm, G, tmp, n2);
+    const double f = lanczos_start(z, n2[0], m, c, blockIdx.x == 0 && threadIdx.x == 0);
+    const int64_t col = (int64_t)c * S.D, step = (int64_t)gridDim.x * RB;
+    for (int64_t r = (int64_t)blockIdx.x * RB + threadIdx.x; r < S.D; r += step) {
+        const cplx<R> v = psi[col + r];
+        cplx<R> o;
+        o.re = (R)(f * (double)v.re);
+        o.im = (R)(f * (double)v.im);
+        V[col + r] = o;
+    }
+}
+
+// The end of Lanczos iteration j: alpha_j from the two projections' partial
+// sums (entry `at` of n per workgroup), beta_j from those of ||w||^2, and V_{j+1}
+// = w / beta_j.  The last iteration only stores the scalars, and everything to
+// the host mirror.
+template <typename R>
+__global__ void __launch_bounds__(RB) k_lanczos_next(const cplx<R>* __restrict__ w, cplx<R>* __restrict__ out,
+                                                     const double* __restrict__ p1, int G1,
+                                                     const double* __restrict__ p2, int G2, int n, int at,
+                                                     const double* __restrict__ norm, int Gn, int j, int m, Shape S,
+                                                     LanczosScalars z)
+{
+    __shared__ double tmp[RB], n2[1], red[kWaves * 2];
+    const int c = blockIdx.y;
+    sum_partials<1>(norm, Gn, tmp, n2);
+    double a[2] = {0.0, 0.0};
+    for (int g = threadIdx.x; g < G1; g += RB) a[0] += p1[((int64_t)c * G1 + g) * n + at];
+    for (int g = threadIdx.x; g < G2; g += RB) a[1] += p2[((int64_t)c * G2 + g) * n + at];
+    const double t = block_sum(a, 2, red);
+    __syncthreads();
+    if (threadIdx.x < 2) tmp[threadIdx.x] = t;
+    __syncthreads();
+    const bool writer = blockIdx.x == 0 && threadIdx.x == 0;
+    const double f = lanczos_scalars(z, tmp[0] + tmp[1], n2[0], j, m, S.B, c, writer);
+    if (j == m - 1) {
+        __syncthreads();   // the writer's stores (same workgroup) before they are read back
+        if (blockIdx.x == 0) lanczos_publish(z, m, S.B, c, threadIdx.x, RB);
+        return;
+    }
+    const int64_t col = (int64_t)c * S.D, step = (int64_t)gridDim.x * RB;
+    for (int64_t r = (int64_t)blockIdx.x * RB + threadIdx.x; r < S.D; r += step) {
+        const cplx<R> v = w[col + r];
+        cplx<R> o;
+        o.re = (R)(f * (double)v.re);
+        o.im = (R)(f * (double)v.im);
+        out[col + r] = o;
+    }
+}
+
+// States of at most kSmallRows rows: everything of a Lanczos iteration after
+// the product in one launch, one workgroup of 16 waves per column with w in LDS.
+// A projection is one wave's work (its lanes over the rows, one butterfly), an
+// update one thread per row; both read the basis from L2.  Bound by one CU's
+// read rate (four reads of the basis, (j + 1) x 16 KiB each at 1,024 complex128
+// rows), which up to 2,048 rows is less than four launches of ~5 us.
+constexpr int kSmallRows = 2048, kSmallThreads = 1024, kSmallMaxM = 512;
+
+template <typename R>
+__global__ void __launch_bounds__(kSmallThreads) k_lanczos_small(const cplx<R>* __restrict__ w, cplx<R>* V,
+                                                                 int64_t vstride, int j, int m, Shape S,
+                                                                 LanczosScalars z)
+{
+    __shared__ cplx<R> ws[kSmallRows];
+    __shared__ double cs[2][2 * kSmallMaxM];   // the projections of the two passes
+    __shared__ double red[kSmallThreads / 64];
+    const int c = blockIdx.y, K = j + 1, D = (int)S.D;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int64_t col = (int64_t)c * S.D;
+    const cplx<R>* Vc = V + col;
+    for (int r = t; r < D; r += kSmallThreads) ws[r] = w[col + r];
+    __syncthreads();
+    double nrm = 0.0;
+    for (int pass = 0; pass < 2; ++pass) {
+        for (int k = wave; k < K; k += kSmallThreads / 64) {
+            const cplx<R>* v = Vc + k * vstride;
+            double ar = 0.0, ai = 0.0;
+#pragma unroll 8
+            for (int r = lane; r < D; r += 64) {
+                const cplx<R> x = v[r], y = ws[r];
+                const double vr = x.re, vi = x.im, br = y.re, bi = y.im;
+                ar += vr * br + vi * bi;
+                ai += vr * bi - vi * br;
+            }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+                ar += __shfl_xor(ar, off, 64);
+                ai += __shfl_xor(ai, off, 64);
+            }
+            if (lane == 0) {
+                cs[pass][2 * k] = ar;
+                cs[pass][2 * k + 1] = ai;
+            }
+        }
+        __syncthreads();
+        for (int r = t; r < D; r += kSmallThreads) {
+            const cplx<R> b = ws[r];
+            double xr = b.re, xi = b.im;
+#pragma unroll 8
+            for (int k = 0; k < K; ++k) {
+                const cplx<R> x = Vc[k * vstride + r];
+                const double cr = cs[pass][2 * k], ci = cs[pass][2 * k + 1];
+                xr -= cr * x.re - ci * x.im;
+                xi -= cr * x.im + ci * x.re;
+            }
+            cplx<R> o;
+            o.re = (R)xr;
+            o.im = (R)xi;
+            ws[r] = o;
+            const double orr = o.re, oi = o.im;
+            if (pass == 1) nrm += orr * orr + oi * oi;
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) nrm += __shfl_xor(nrm, off, 64);
+    if (lane == 0) red[wave] = nrm;
+    __syncthreads();
+    double wn = 0.0;
+    for (int i = 0; i < kSmallThreads / 64; ++i) wn += red[i];
+    const double f = lanczos_scalars(z, cs[0][2 * j] + cs[1][2 * j], wn, j, m, S.B, c, t == 0);
+    if (j == m - 1) {
+        __syncthreads();
+        lanczos_publish(z, m, S.B, c, t, kSmallThreads);
+        return;
+    }
+    cplx<R>* vn = V + (int64_t)K * vstride + col;
+    for (int r = t; r < D; r += kSmallThreads) {
+        const cplx<R> x = ws[r];
+        cplx<R> o;
+        o.re = (R)(f * (double)x.re);
+        o.im = (R)(f * (double)x.im);
+        vn[r] = o;
+    }
+}
+
+// Coefficients of a combination for one column, passed with the launch.
+struct CombineArg {
+    static constexpr int kMax = 64;
+    double c[2 * kMax];
+};
+
+// y = sum_k c_k V_k for all K vectors; the coefficients come with the launch
+// (one column) or from the device array coef[k][c].
+template <typename R, bool ARG>
+__global__ void __launch_bounds__(RB) k_combine(cplx<R>* y, const cplx<R>* V, int64_t vstride, int K, CombineArg arg,
+                                                const double* __restrict__ coef, Shape S)
 {
     const int c = blockIdx.y;
     const int64_t col = (int64_t)c * S.D;
     const int64_t step = (int64_t)gridDim.x * RB;
+    auto cf = [&](int k, int i) { return ARG ? arg.c[2 * k + i] : coef[((int64_t)k * S.B + c) * 2 + i]; };
     for (int64_t r = (int64_t)blockIdx.x * RB + threadIdx.x; r < S.D; r += step) {
         const int64_t e = col + r;
         double xr = 0.0, xi = 0.0;
@@ -347,13 +537,13 @@ __global__ void __launch_bounds__(RB) k_combine(cplx<R>* __restrict__ y, const c
             for (int u = 0; u < KC; ++u) v[u] = V[(k + u) * vstride + e];
 #pragma unroll
             for (int u = 0; u < KC; ++u) {
-                const double cr = coef[((k + u) * S.B + c) * 2], ci = coef[((k + u) * S.B + c) * 2 + 1];
+                const double cr = cf(k + u, 0), ci = cf(k + u, 1);
                 xr += cr * v[u].re - ci * v[u].im;
                 xi += cr * v[u].im + ci * v[u].re;
             }
         }
         for (; k < K; ++k) {
-            const double cr = coef[(k * S.B + c) * 2], ci = coef[(k * S.B + c) * 2 + 1];
+            const double cr = cf(k, 0), ci = cf(k, 1);
             const cplx<R> v = V[k * vstride + e];
             xr += cr * v.re - ci * v.im;
             xi += cr * v.im + ci * v.re;
@@ -371,33 +561,6 @@ VecOps::VecOps(syk_terms_s& h, syk_dtype dt, int64_t dim, int nvec, hipStream_t 
     : h_(h), dt_(dt), dim_(dim), nvec_(nvec), s_(s)
 {
     require(nvec >= 1 && nvec <= 65535, "nvec must be in [1, 65535]");
-}
-
-void* VecOps::upload(const std::vector<zd>& c)
-{
-    std::vector<double> flat(2 * c.size());
-    std::memcpy(flat.data(), c.data(), flat.size() * sizeof(double));
-    return upload(flat);
-}
-
-void* VecOps::upload(const std::vector<double>& c)
-{
-    // A synchronous copy from the caller's host vector (a few hundred bytes):
-    // when it returns, all earlier work on the stream has finished, so the
-    // device slot can be reused freely.
-    void* d = h_.ws.get("upload" + std::to_string(h_.upload_slot++ % 8), c.size() * sizeof(double));
-    SYK_HIP(hipMemcpyAsync(d, c.data(), c.size() * sizeof(double), hipMemcpyHostToDevice, s_));
-    SYK_HIP(hipStreamSynchronize(s_));
-    return d;
-}
-
-template <typename T>
-std::vector<T> VecOps::download(const void* dev, size_t n)
-{
-    std::vector<T> out(n);
-    SYK_HIP(hipMemcpyAsync(out.data(), dev, n * sizeof(T), hipMemcpyDeviceToHost, s_));
-    SYK_HIP(hipStreamSynchronize(s_));
-    return out;
 }
 
 void VecOps::majorana(int a, const void* in, void* out)
@@ -423,69 +586,117 @@ void VecOps::majorana_sector(int a, int top, int s_in, const void* in, void* out
     SYK_HIP(hipGetLastError());
 }
 
-const double* VecOps::multidot_dev(const void* V, int K, const void* w, const char* slot)
+// Workgroups per column of a reduction and, for large blocks, the finishing
+// kernel: G partial sums of n doubles per column become 1.  Up to kFusedRows
+// rows in all, a column's reduction takes at most kMaxFusedGroups workgroups and
+// each kernel that uses the sums adds them itself, three launches of ~5 us less
+// per Lanczos iteration (N=32, m=30: 3.63 -> 3.35 ms a step; N=20: 61 -> 26 ms an
+// OTOC curve, with the one-launch iteration).  Larger blocks need more workgroups
+// to stream at HBM speed and there a finishing launch is less than every
+// workgroup's own sum (64 complex64 columns at N=36: 134.4 ms a step without it,
+// 133.6 with).
+constexpr int kMaxFusedGroups = 256;
+constexpr int64_t kFusedRows = (int64_t)1 << 18;
+
+dim3 VecOps::reduce_grid() const
 {
     Shape S{dim_, nvec_};
     dim3 g = grid_of(S, true);
-    const int B = nvec_;
-    double* out = (double*)h_.ws.get(slot, (size_t)std::max(K, kFusedMax) * B * 2 * sizeof(double));
-    for (int k0 = 0; k0 < K; k0 += KC) {
-        const int kk = std::min(KC, K - k0);
-        double* part = (double*)h_.ws.get("md_part", (size_t)g.x * kk * B * 2 * sizeof(double));
-        const size_t off = (size_t)k0 * vec_bytes();
-        with_count<KC>(kk, [&](auto kc) {
-            constexpr int K_ = decltype(kc)::value;
-            if (dt_ == SYK_C128)
-                hipLaunchKernelGGL((k_multidot<double, K_>), g, dim3(RB), 0, s_,
-                                   (const c128*)((const char*)V + off), dim_ * B, (const c128*)w, S, part);
-            else
-                hipLaunchKernelGGL((k_multidot<float, K_>), g, dim3(RB), 0, s_,
-                                   (const c64*)((const char*)V + off), dim_ * B, (const c64*)w, S, part);
-        });
-        SYK_HIP(hipGetLastError());
-        const int n = kk * B * 2;
-        launch_finish(part, (int)g.x, n, out + (size_t)k0 * B * 2, s_);
-        SYK_HIP(hipGetLastError());
-    }
-    return out;
+    if (dim_ * nvec_ <= kFusedRows && g.x > (unsigned)kMaxFusedGroups) g.x = kMaxFusedGroups;
+    return g;
 }
 
-std::vector<zd> VecOps::fetch(const double* dev, int K)
+VecOps::Sums VecOps::finished(const double* part, int G, int n, const char* slot)
 {
-    const size_t n = (size_t)K * nvec_;
-    std::vector<double> flat = download<double>(dev, 2 * n);
-    std::vector<zd> res(n);
-    for (size_t i = 0; i < n; ++i) res[i] = zd(flat[2 * i], flat[2 * i + 1]);
-    return res;
+    if (dim_ * nvec_ <= kFusedRows && G <= kMaxFusedGroups) return Sums{part, G};
+    double* out = (double*)h_.ws.get(slot, (size_t)2 * kFusedMax * nvec_ * sizeof(double));
+    hipLaunchKernelGGL(k_finish, dim3(n, nvec_), dim3(64), 0, s_, part, G, n, out);
+    SYK_HIP(hipGetLastError());
+    return Sums{out, 1};
+}
+
+// <V_k | w> for k in [k0, k0 + kk) as partial sums in `slot` (kk <= kFusedMax).
+VecOps::Sums VecOps::dots(const void* V, int k0, int kk, const void* w, const std::string& slot)
+{
+    Shape S{dim_, nvec_};
+    const dim3 g = reduce_grid();
+    // sized for a full chunk: no reallocation as a basis grows
+    double* part = (double*)h_.ws.get(slot, (size_t)g.x * kFusedMax * nvec_ * 2 * sizeof(double));
+    const char* v = (const char*)V + (size_t)k0 * vec_bytes();
+    const int64_t vs = dim_ * nvec_;
+    with_count<kFusedMax>(kk, [&](auto kc) {
+        constexpr int K_ = decltype(kc)::value;
+        if (dt_ == SYK_C128)
+            hipLaunchKernelGGL((k_multidot<double, K_>), g, dim3(RB), 0, s_, (const c128*)v, vs, (const c128*)w, S, part);
+        else
+            hipLaunchKernelGGL((k_multidot<float, K_>), g, dim3(RB), 0, s_, (const c64*)v, vs, (const c64*)w, S, part);
+    });
+    SYK_HIP(hipGetLastError());
+    return finished(part, (int)g.x, 2 * kk, (slot + "_f").c_str());
+}
+
+// w -= sum_k c_k V_k for k in [k0, k0 + kk), c the sums of p; with norm_slot,
+// the partial sums of ||w||^2.
+VecOps::Sums VecOps::subtract(void* w, const void* V, int k0, int kk, Sums p, const char* norm_slot)
+{
+    Shape S{dim_, nvec_};
+    const dim3 g = reduce_grid();
+    double* part = norm_slot ? (double*)h_.ws.get(norm_slot, (size_t)g.x * kFusedMax * nvec_ * 2 * sizeof(double)) : nullptr;
+    const char* v = (const char*)V + (size_t)k0 * vec_bytes();
+    const int64_t vs = dim_ * nvec_;
+    with_count<kFusedMax>(kk, [&](auto kc) {
+        constexpr int K_ = decltype(kc)::value;
+        if (dt_ == SYK_C128)
+            hipLaunchKernelGGL((k_update<double, K_>), g, dim3(RB), 0, s_, (c128*)w, (const c128*)v, vs, p.p, p.G, S, part);
+        else
+            hipLaunchKernelGGL((k_update<float, K_>), g, dim3(RB), 0, s_, (c64*)w, (const c64*)v, vs, p.p, p.G, S, part);
+    });
+    SYK_HIP(hipGetLastError());
+    if (!norm_slot) return Sums{nullptr, 0};
+    return finished(part, (int)g.x, 1, (std::string(norm_slot) + "_f").c_str());
+}
+
+// The first update and the second projection in one sweep (K <= kFusedMax).
+VecOps::Sums VecOps::subtract_dots(void* w, const void* V, int K, Sums p, const std::string& slot)
+{
+    Shape S{dim_, nvec_};
+    const dim3 g = reduce_grid();
+    double* part = (double*)h_.ws.get(slot, (size_t)g.x * kFusedMax * nvec_ * 2 * sizeof(double));
+    const int64_t vs = dim_ * nvec_;
+    with_count<kFusedMax>(K, [&](auto kc) {
+        constexpr int K_ = decltype(kc)::value;
+        if (dt_ == SYK_C128)
+            hipLaunchKernelGGL((k_update_dot<double, K_>), g, dim3(RB), 0, s_, (c128*)w, (const c128*)V, vs, p.p, p.G, S, part);
+        else
+            hipLaunchKernelGGL((k_update_dot<float, K_>), g, dim3(RB), 0, s_, (c64*)w, (const c64*)V, vs, p.p, p.G, S, part);
+    });
+    SYK_HIP(hipGetLastError());
+    return finished(part, (int)g.x, 2 * K, (slot + "_f").c_str());
 }
 
 std::vector<zd> VecOps::multidot(const void* V, int K, const void* w)
 {
-    return fetch(multidot_dev(V, K, w, "md_out"), K);
-}
-
-const double* VecOps::update_dot(void* w, const void* V, int K, const double* c1, const char* slot)
-{
-    if (K < 1 || K > kFusedMax) throw Error(SYK_EINVAL, "update_dot: unsupported basis size");
-    Shape S{dim_, nvec_};
-    dim3 g = grid_of(S, true);
-    const int B = nvec_;
-    double* part = (double*)h_.ws.get("ud_part", (size_t)g.x * kFusedMax * B * 2 * sizeof(double));
-    double* out = (double*)h_.ws.get(slot, (size_t)kFusedMax * B * 2 * sizeof(double));
-    const int64_t vs = dim_ * B;
-    with_count<kFusedMax>(K, [&](auto kc) {
-        constexpr int K_ = decltype(kc)::value;
-        if (dt_ == SYK_C128)
-            hipLaunchKernelGGL((k_update_dot<double, K_>), g, dim3(RB), 0, s_, (c128*)w, (const c128*)V, vs, c1, S,
-                               part);
-        else
-            hipLaunchKernelGGL((k_update_dot<float, K_>), g, dim3(RB), 0, s_, (c64*)w, (const c64*)V, vs, c1, S, part);
-    });
-    SYK_HIP(hipGetLastError());
-    const int n = K * B * 2;
-    launch_finish(part, (int)g.x, n, out, s_);
-    SYK_HIP(hipGetLastError());
-    return out;
+    const size_t n = (size_t)K * nvec_;
+    double* host = (double*)h_.pinned.get(2 * n * sizeof(double));
+    for (int k0 = 0; k0 < K; k0 += kFusedMax) {
+        const int kk = std::min(kFusedMax, K - k0);
+        Sums p = dots(V, k0, kk, w, "md_part");
+        hipLaunchKernelGGL(k_finish, dim3(2 * kk, nvec_), dim3(64), 0, s_, p.p, p.G, 2 * kk,
+                           host + 2 * (size_t)k0 * nvec_);
+        SYK_HIP(hipGetLastError());
+    }
+    SYK_HIP(hipStreamSynchronize(s_));
+    std::vector<zd> res(n);
+    for (int k0 = 0; k0 < K; k0 += kFusedMax) {   // host: [chunk][column][k]
+        const int kk = std::min(kFusedMax, K - k0);
+        const double* h = host + 2 * (size_t)k0 * nvec_;
+        for (int c = 0; c < nvec_; ++c)
+            for (int k = 0; k < kk; ++k) {
+                const double* x = h + 2 * ((size_t)c * kk + k);
+                res[(size_t)(k0 + k) * nvec_ + c] = zd(x[0], x[1]);
+            }
+    }
+    return res;
 }
 
 std::vector<double> VecOps::norm2(const void* a)
@@ -496,99 +707,105 @@ std::vector<double> VecOps::norm2(const void* a)
     return out;
 }
 
-std::vector<double> VecOps::update(void* w, const void* V, int K, const std::vector<zd>& coef, bool want_norm)
+bool VecOps::small_lanczos(int m) const { return dim_ <= kSmallRows && m <= kSmallMaxM; }
+
+LanczosScalars VecOps::lanczos_begin(const void* psi, void* V, int m)
 {
-    return update_dev(w, V, K, (const double*)upload(coef), want_norm);
+    const size_t B = (size_t)nvec_, mB = (size_t)m * B;
+    double* d = (double*)h_.ws.get("lz_dbl", (3 * mB + 2 * B) * sizeof(double));
+    int* i = (int*)h_.ws.get("lz_int", (mB + 2 * B) * sizeof(int));
+    double* h = (double*)h_.pinned.get((2 * mB + B) * sizeof(double) + 2 * B * sizeof(int));
+    LanczosScalars z{};
+    z.alpha = d;
+    z.beta = d + mB;
+    z.scale = d + 2 * mB;          // [m + 1][B]
+    z.nrm = d + 3 * mB + B;
+    z.kdim = i;                    // [m + 1][B]
+    z.flag = i + mB + B;
+    z.h_alpha = h;
+    z.h_beta = h + mB;
+    z.h_nrm = h + 2 * mB;
+    z.h_kdim = (int*)(h + 2 * mB + B);
+    z.h_flag = z.h_kdim + B;
+    Shape S{dim_, nvec_};
+    const Sums n = dots(psi, 0, 1, psi, "gs_n");
+    const dim3 g = grid_of(S, false);
+    if (dt_ == SYK_C128)
+        hipLaunchKernelGGL(k_lanczos_start<double>, g, dim3(RB), 0, s_, (const c128*)psi, (c128*)V, n.p, n.G, m, S, z);
+    else
+        hipLaunchKernelGGL(k_lanczos_start<float>, g, dim3(RB), 0, s_, (const c64*)psi, (c64*)V, n.p, n.G, m, S, z);
+    SYK_HIP(hipGetLastError());
+    return z;
 }
 
-std::vector<double> VecOps::update_dev(void* w, const void* V, int K, const double* dcoef, bool want_norm)
-{
-    const double* n = update_dev_norm(w, V, K, dcoef, want_norm);
-    if (!want_norm) return {};
-    return download<double>(n, nvec_);
-}
-
-const double* VecOps::update_dev_norm(void* w, const void* V, int K, const double* dcoef, bool want_norm)
+void VecOps::lanczos_step(void* w, void* V, int j, int m, const LanczosScalars& z)
 {
     Shape S{dim_, nvec_};
-    const int B = nvec_;
-    dim3 g = grid_of(S, true);
-    double* part = want_norm ? (double*)h_.ws.get("up_part", (size_t)g.x * B * sizeof(double)) : nullptr;
-    for (int k0 = 0; k0 < K; k0 += KC) {
-        const int kk = std::min(KC, K - k0);
-        const bool last = k0 + KC >= K;
-        const size_t off = (size_t)k0 * vec_bytes();
-        double* p = (last && want_norm) ? part : nullptr;
-        with_count<KC>(kk, [&](auto kc) {
-            constexpr int K_ = decltype(kc)::value;
-            if (dt_ == SYK_C128)
-                hipLaunchKernelGGL((k_update<double, K_>), g, dim3(RB), 0, s_, (c128*)w,
-                                   (const c128*)((const char*)V + off), dim_ * B, dcoef + (size_t)k0 * B * 2, S, p);
-            else
-                hipLaunchKernelGGL((k_update<float, K_>), g, dim3(RB), 0, s_, (c64*)w,
-                                   (const c64*)((const char*)V + off), dim_ * B, dcoef + (size_t)k0 * B * 2, S, p);
-        });
+    const int K = j + 1;
+    const int64_t vs = dim_ * nvec_;
+    if (small_lanczos(m)) {
+        const dim3 g(1, nvec_);
+        if (dt_ == SYK_C128)
+            hipLaunchKernelGGL(k_lanczos_small<double>, g, dim3(kSmallThreads), 0, s_, (const c128*)w, (c128*)V, vs, j, m, S, z);
+        else
+            hipLaunchKernelGGL(k_lanczos_small<float>, g, dim3(kSmallThreads), 0, s_, (const c64*)w, (c64*)V, vs, j, m, S, z);
         SYK_HIP(hipGetLastError());
+        return;
     }
-    if (!want_norm) return nullptr;
-    double* out = (double*)h_.ws.get("up_out", (size_t)B * sizeof(double));
-    launch_finish(part, (int)g.x, B, out, s_);
-    SYK_HIP(hipGetLastError());
-    return out;
-}
-
-void VecOps::lanczos_coef(const double* c1, const double* c2, const double* wnorm2, int j, int m, LanczosScalars& z)
-{
-    const int B = nvec_;
-    hipLaunchKernelGGL(k_lanczos_coef, dim3((B + 255) / 256), dim3(256), 0, s_, c1, c2, wnorm2, j, m, B, z.alpha,
-                       z.beta, z.kdim, z.scale, z.nrm, z.f, z.flag);
-    SYK_HIP(hipGetLastError());
-}
-
-void VecOps::scale_dev(void* out, const void* in, const double* df)
-{
-    Shape S{dim_, nvec_};
-    dim3 g = grid_of(S, false);
+    // two passes of classical Gram-Schmidt in chunks of kFusedMax basis vectors;
+    // k0: the chunk that holds the newest vector
+    const int nch = (K + kFusedMax - 1) / kFusedMax, k0 = (nch - 1) * kFusedMax, kl = K - k0;
+    auto count = [&](int i) { return std::min(kFusedMax, K - i * kFusedMax); };
+    auto slot = [](const char* s, int i) { return s + std::to_string(i); };
+    std::vector<Sums> p1(nch), p2(nch);
+    for (int i = 0; i < nch; ++i) p1[i] = dots(V, i * kFusedMax, count(i), w, slot("gs_p", i));
+    if (nch == 1) {
+        p2[0] = subtract_dots(w, V, K, p1[0], "gs_q0");
+    } else {
+        for (int i = 0; i < nch; ++i) subtract(w, V, i * kFusedMax, count(i), p1[i], nullptr);
+        for (int i = 0; i < nch; ++i) p2[i] = dots(V, i * kFusedMax, count(i), w, slot("gs_q", i));
+    }
+    Sums n{};
+    for (int i = 0; i < nch; ++i) n = subtract(w, V, i * kFusedMax, count(i), p2[i], i == nch - 1 ? "gs_n" : nullptr);
+    const dim3 g = j == m - 1 ? dim3(1, nvec_) : grid_of(S, false);
+    void* out = (char*)V + (size_t)K * vec_bytes();   // not written by the last iteration
+    const int at = 2 * (kl - 1);
     if (dt_ == SYK_C128)
-        hipLaunchKernelGGL(k_scale<double>, g, dim3(RB), 0, s_, (c128*)out, (const c128*)in, df, S);
+        hipLaunchKernelGGL(k_lanczos_next<double>, g, dim3(RB), 0, s_, (const c128*)w, (c128*)out, p1[nch - 1].p,
+                           p1[nch - 1].G, p2[nch - 1].p, p2[nch - 1].G, 2 * kl, at, n.p, n.G, j, m, S, z);
     else
-        hipLaunchKernelGGL(k_scale<float>, g, dim3(RB), 0, s_, (c64*)out, (const c64*)in, df, S);
+        hipLaunchKernelGGL(k_lanczos_next<float>, g, dim3(RB), 0, s_, (const c64*)w, (c64*)out, p1[nch - 1].p,
+                           p1[nch - 1].G, p2[nch - 1].p, p2[nch - 1].G, 2 * kl, at, n.p, n.G, j, m, S, z);
     SYK_HIP(hipGetLastError());
 }
 
-void VecOps::to_device(void* dev, const void* host, size_t bytes)
-{
-    SYK_HIP(hipMemcpyAsync(dev, host, bytes, hipMemcpyHostToDevice, s_));
-    SYK_HIP(hipStreamSynchronize(s_));
-}
-
-void VecOps::to_host(void* host, const void* dev, size_t bytes)
-{
-    SYK_HIP(hipMemcpyAsync(host, dev, bytes, hipMemcpyDeviceToHost, s_));
-    SYK_HIP(hipStreamSynchronize(s_));
-}
-
-void VecOps::scale(void* out, const void* in, const std::vector<double>& f)
-{
-    Shape S{dim_, nvec_};
-    dim3 g = grid_of(S, false);
-    double* df = (double*)upload(f);
-    if (dt_ == SYK_C128)
-        hipLaunchKernelGGL(k_scale<double>, g, dim3(RB), 0, s_, (c128*)out, (const c128*)in, df, S);
-    else
-        hipLaunchKernelGGL(k_scale<float>, g, dim3(RB), 0, s_, (c64*)out, (const c64*)in, df, S);
-    SYK_HIP(hipGetLastError());
-}
+void VecOps::synchronize() { SYK_HIP(hipStreamSynchronize(s_)); }
 
 void VecOps::combine(void* y, const void* V, int K, const std::vector<zd>& coef)
 {
     Shape S{dim_, nvec_};
     dim3 g = grid_of(S, false);
-    double* dcoef = (double*)upload(coef);
-    if (dt_ == SYK_C128)
-        hipLaunchKernelGGL(k_combine<double>, g, dim3(RB), 0, s_, (c128*)y, (const c128*)V, dim_ * nvec_, K, dcoef, S);
-    else
-        hipLaunchKernelGGL(k_combine<float>, g, dim3(RB), 0, s_, (c64*)y, (const c64*)V, dim_ * nvec_, K, dcoef, S);
+    CombineArg arg{};
+    const double* dc = nullptr;
+    const int64_t vs = dim_ * nvec_;
+    if (nvec_ == 1 && K <= CombineArg::kMax) {
+        std::memcpy(arg.c, coef.data(), (size_t)K * sizeof(zd));
+        if (dt_ == SYK_C128)
+            hipLaunchKernelGGL((k_combine<double, true>), g, dim3(RB), 0, s_, (c128*)y, (const c128*)V, vs, K, arg, dc, S);
+        else
+            hipLaunchKernelGGL((k_combine<float, true>), g, dim3(RB), 0, s_, (c64*)y, (const c64*)V, vs, K, arg, dc, S);
+    } else {
+        // A copy from pageable memory the call owns: it has left the host buffer
+        // when the call returns.
+        double* d = (double*)h_.ws.get("combine_coef", coef.size() * sizeof(zd));
+        SYK_HIP(hipMemcpyAsync(d, coef.data(), coef.size() * sizeof(zd), hipMemcpyHostToDevice, s_));
+        SYK_HIP(hipStreamSynchronize(s_));
+        dc = d;
+        if (dt_ == SYK_C128)
+            hipLaunchKernelGGL((k_combine<double, false>), g, dim3(RB), 0, s_, (c128*)y, (const c128*)V, vs, K, arg, dc, S);
+        else
+            hipLaunchKernelGGL((k_combine<float, false>), g, dim3(RB), 0, s_, (c64*)y, (const c64*)V, vs, K, arg, dc, S);
+    }
     SYK_HIP(hipGetLastError());
 }
 

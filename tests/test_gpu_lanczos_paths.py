@@ -1,0 +1,43 @@
+"""The Lanczos iteration's launch paths against exact exponentials in plain
+torch: states of at most 2,048 rows (one launch per iteration) and just above,
+bases below, at and above the 16 vectors one sweep serves, single columns and
+blocks, in both precisions; and a zero column, which stays zero."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import native
+from paper_2002_05725_amd import api, inputs
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+TOL = {torch.complex128: 1e-10, torch.complex64: 2e-5}
+
+
+def _taylor(H, psi, z):
+    y = term = psi
+    for k in range(1, 40):
+        term = z / k * H(term)
+        y = y + term
+    return y
+
+
+@pytest.mark.parametrize("dtype", list(TOL))
+@pytest.mark.parametrize("N,nvec,m", [(8, 1, 12), (20, 1, 16), (22, 2, 17), (22, 1, 33), (24, 1, 15), (24, 3, 20)])
+def test_step_matches_exponential(N, nvec, m, dtype):
+    J = inputs.couplings(N, 5)
+    psi = np.stack([inputs.typical_state(N, 50 + c) for c in range(nvec)])
+    if nvec > 1:
+        psi[1] = 0.0
+    T = api.Terms(N, J)
+    x = torch.from_numpy(psi).to(DEV).to(dtype)
+    api.krylov_expmv(T, x, -1j, 0.4, m=m, dt=0.4)
+    y = x.cpu().numpy().astype(np.complex128)
+    sp = native.SparseH(N, J)
+    for c in range(nvec):
+        ref = _taylor(sp, psi[c], -0.4j)
+        print(f"[lanczos] N={N} column {c} of {nvec} m={m} {dtype}", flush=True)
+        assert np.linalg.norm(y[c] - ref) <= TOL[dtype] * max(1.0, np.linalg.norm(ref))
+        if nvec > 1 and c == 1:
+            assert not y[c].any()
+    T.close()
