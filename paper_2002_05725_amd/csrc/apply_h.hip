@@ -666,6 +666,175 @@ __global__ void __launch_bounds__(256) k_diag_fill(const uint32_t* __restrict__ 
     diag[(uint64_t)blockIdx.y * dim + r] = s;
 }
 
+// Coefficient table of small states: D_x(r) itself, for every mask and row, in
+// the order k_apply_table reads it: [realisation][row block][mask][kTableRows].
+constexpr int kTableRows = 16, kTableThreads = 1024, kTableSlots = kTableThreads / kTableRows;
+constexpr int kTableMaxBits = 12;
+constexpr size_t kTableBytes = (size_t)40 << 20, kTableTraffic = (size_t)64 << 20;
+
+template <typename R>
+__global__ void __launch_bounds__(256) k_table_fill(KTerms<double> T, const MaskRec* __restrict__ masks, int n_masks,
+                                                    const uint32_t* __restrict__ dz, const double* __restrict__ dw,
+                                                    int n_diag, uint32_t dim, uint32_t n_blocks,
+                                                    cplx<R>* __restrict__ table)
+{
+    const uint64_t e = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= (uint64_t)n_blocks * n_masks * kTableRows) return;
+    const uint32_t m = (uint32_t)(e / kTableRows) % (uint32_t)n_masks;
+    const uint32_t r = (uint32_t)(e / ((uint64_t)kTableRows * n_masks)) * kTableRows + (uint32_t)(e % kTableRows);
+    const int rc = blockIdx.y;
+    const MaskRec mk = masks[m];
+    const uint32_t type = mk.type_tab >> 28, tab = mk.type_tab & 0x0fffffffu;
+    double re = 0.0, im = 0.0;
+    if (r < dim) {
+        if (type == MASK_QUAD) {
+            const c128 t = T.tab4[((size_t)tab * T.n_real + rc) * 16 + quad_index(r, mk.qpack)];
+            re = t.re;
+            im = t.im;
+        } else if (type == MASK_PAIR) {
+            // placeholder qubits (31) read as 0
+            const uint32_t idx = bit(r, mask_q(mk.qpack, 0)) | (bit(r, mask_q(mk.qpack, 1)) << 1);
+            for (int k = 0; k < 4; ++k) {
+                const double* w = T.w2 + (((size_t)tab * T.n_real + rc) * 4 + k) * (T.M + 1);
+                double l = w[T.M];
+                for (int c = 0; c < T.M; ++c)
+                    if ((r >> c) & 1u) l += w[c];
+                const c128 ph = T.phi2[(size_t)tab * 16 + idx * 4 + k];
+                re += ph.re * l;
+                im += ph.im * l;
+            }
+        } else {
+            const double* d = dw + (size_t)rc * n_diag;
+            for (int n = 0; n < n_diag; ++n) re += parity(r & dz[n]) ? -d[n] : d[n];
+        }
+        const uint32_t sg = type == MASK_DIAG ? 0u : parity(r & mk.zbase);
+        re = flip(re, sg);
+        im = flip(im, sg);
+    }
+    cplx<R> o;
+    o.re = (R)re;
+    o.im = (R)im;
+    table[(uint64_t)rc * n_blocks * n_masks * kTableRows + e] = o;
+}
+
+struct KColumns {
+    int32_t real[kColsPerLaunch];
+};
+
+// H psi of a small state from its coefficient table: one multiply-add per
+// (row, mask), FP64 sums.  A workgroup owns 16 rows of one column, and 64 groups
+// of 16 threads take every 64th mask, so that 2^8 .. 2^12 rows keep 16 .. 256
+// workgroups of 16 waves in flight with a few masks each; the groups' sums are
+// added in a fixed order.  Bound by its loads' latency (table entry, mask, then
+// the amplitude), up to 2^12 rows by the table's bytes from L2 and the
+// Infinity Cache (37 MB at N=24 in complex128).
+template <typename R>
+__global__ void __launch_bounds__(kTableThreads) k_apply_table(const cplx<R>* __restrict__ table,
+                                                               const MaskRec* __restrict__ masks, int n_masks,
+                                                               KColumns C, uint32_t dim,
+                                                               const cplx<R>* __restrict__ psi, cplx<R>* __restrict__ out)
+{
+    __shared__ c128 red[kTableThreads / 64][kTableRows];
+    const uint32_t tid = threadIdx.x, rl = tid % kTableRows, slot = tid / kTableRows;
+    const uint32_t r = blockIdx.x * kTableRows + rl;
+    const int rc = C.real[blockIdx.y];
+    const cplx<R>* t = table + ((uint64_t)rc * gridDim.x + blockIdx.x) * n_masks * kTableRows + tid;
+    psi += (uint64_t)blockIdx.y * dim;
+    double ar = 0.0, ai = 0.0;
+    if (r < dim) {
+#pragma unroll 4
+        for (int m = (int)slot; m < n_masks; m += kTableSlots) {
+            const cplx<R> d = *t;
+            t += kTableThreads;
+            const cplx<R> v = psi[r ^ masks[m].x];
+            const double dr = d.re, di = d.im, vr = v.re, vi = v.im;
+            ar = fma(dr, vr, ar);
+            ar = fma(-di, vi, ar);
+            ai = fma(dr, vi, ai);
+            ai = fma(di, vr, ai);
+        }
+    }
+    // the four groups of a wave, then the waves in order
+#pragma unroll
+    for (int off = kTableRows; off < 64; off <<= 1) {
+        ar += __shfl_xor(ar, off, 64);
+        ai += __shfl_xor(ai, off, 64);
+    }
+    if ((tid & 63u) < kTableRows) red[tid >> 6][rl] = c128{ar, ai};
+    __syncthreads();
+    if (tid < kTableRows && r < dim) {
+        double sr = 0.0, si = 0.0;
+#pragma unroll
+        for (int w = 0; w < kTableThreads / 64; ++w) {
+            sr += red[w][rl].re;
+            si += red[w][rl].im;
+        }
+        cplx<R> o;
+        o.re = (R)sr;
+        o.im = (R)si;
+        out[(uint64_t)blockIdx.y * dim + r] = o;
+    }
+}
+
+uint32_t table_blocks(const HamiltonianDev& H)
+{
+    return ((1u << H.M) + kTableRows - 1) / kTableRows;
+}
+
+size_t table_entries(const HamiltonianDev& H)
+{
+    return (size_t)table_blocks(H) * kTableRows * H.host_masks->size();
+}
+
+// Whether a product runs from the coefficient table: states of at most 2^12
+// rows whose table over all realisations fits kTableBytes, and few enough
+// columns that reading it once per column (kTableTraffic) stays cheaper than
+// forming the coefficients; never when the caller has chosen a tile.
+bool use_table(const HamiltonianDev& H, const ApplyPlan& P, int nvec, size_t esz)
+{
+    if (P.fixed_tile || H.M > kTableMaxBits) return false;
+    const size_t one = table_entries(H) * esz;
+    return one * H.n_real <= kTableBytes && one * std::min(nvec, kColsPerLaunch) <= kTableTraffic;
+}
+
+// Builds the table of an element type the first time it is needed.
+template <typename R>
+void ensure_table(const HamiltonianDev& H, DevBuf& buf, hipStream_t s)
+{
+    if (buf.p) return;
+    const size_t n = table_entries(H);
+    buf.ensure(n * H.n_real * sizeof(cplx<R>));
+    KTerms<double> T{H.tab4_d, H.qinfo, H.phi2_d, H.w2_d, nullptr, H.n_real, H.M};
+    hipLaunchKernelGGL(k_table_fill<R>, dim3((uint32_t)((n + 255) / 256), (uint32_t)H.n_real), dim3(256), 0, s, T, H.masks,
+                       (int)H.host_masks->size(), H.dz, H.dw_d, H.n_diag, 1u << H.M, table_blocks(H), buf.as<cplx<R>>());
+    SYK_HIP(hipGetLastError());
+    SYK_HIP(hipStreamSynchronize(s));   // once per handle: later calls may come on other streams
+}
+
+template <typename R>
+void launch_table(const HamiltonianDev& H, const DevBuf& table, int nvec, const int32_t* real_of_col, const void* psi,
+                  void* out, hipStream_t s)
+{
+    const uint32_t dim = 1u << H.M;
+    for (int c0 = 0; c0 < nvec; c0 += kColsPerLaunch) {
+        KColumns C{};
+        const int n = std::min(kColsPerLaunch, nvec - c0);
+        for (int c = 0; c < n; ++c) C.real[c] = real_of_col ? real_of_col[c0 + c] : 0;
+        hipLaunchKernelGGL(k_apply_table<R>, dim3(table_blocks(H), (uint32_t)n), dim3(kTableThreads), 0, s,
+                           table.as<cplx<R>>(), H.masks, (int)H.host_masks->size(), C, dim,
+                           static_cast<const cplx<R>*>(psi) + (uint64_t)c0 * dim,
+                           static_cast<cplx<R>*>(out) + (uint64_t)c0 * dim);
+        SYK_HIP(hipGetLastError());
+    }
+}
+
+void launch_table_any(const HamiltonianDev& H, syk_dtype dtype, int nvec, const int32_t* real_of_col, const void* psi,
+                      void* out, hipStream_t s)
+{
+    if (dtype == SYK_C128) launch_table<double>(H, H.table_d, nvec, real_of_col, psi, out, s);
+    else launch_table<float>(H, H.table_f, nvec, real_of_col, psi, out, s);
+}
+
 // Fills H.diag the first time it is needed (on the stream, then waits for it).
 void ensure_diag(const HamiltonianDev& H, hipStream_t s)
 {
@@ -1101,7 +1270,8 @@ ApplyPlan plan_apply(int M, int nvec, syk_dtype dtype, const ApplyTuning* tune)
     // A shape given by the caller is run as it is given, unsplit.
     int tb = std::min(M, 11);
     P.parts = 1;
-    if (tune && tune->tile_bits > 0) {
+    P.fixed_tile = tune && tune->tile_bits > 0;
+    if (P.fixed_tile) {
         tb = std::min(tune->tile_bits, M);
     } else {
         const int64_t wg = ((int64_t)1 << (M - tb)) * std::min(nvec, kColsPerLaunch);
@@ -1177,6 +1347,13 @@ void launch_apply_h_noalloc(const HamiltonianDev& H, int device, syk_dtype dtype
 {
     const size_t esz = elem_bytes(dtype);
     const uint64_t dim = (uint64_t)1 << H.M;
+    if (use_table(H, P, nvec, esz)) {
+        if (!(dtype == SYK_C128 ? H.table_d : H.table_f).p)
+            throw Error(SYK_EINVAL, "apply_H_noalloc: the handle has no tables for this dtype and block width yet "
+                                    "(call syk_apply_H once with them first)");
+        launch_table_any(H, dtype, nvec, real_of_col, psi, out, s);
+        return;
+    }
     const size_t half = (size_t)std::min(nvec, kColsPerLaunch) * dim * esz;
     const size_t rot = P.two_layouts ? 2 * half : 0, part = parts_bytes(P, nvec, dim);
     if (rot + part > kNoAllocScratchBytes)
@@ -1196,6 +1373,14 @@ void launch_apply_h_noalloc(const HamiltonianDev& H, int device, syk_dtype dtype
 void launch_apply_h(const HamiltonianDev& H, syk_dtype dtype, int nvec, const int32_t* real_of_col,
                     const void* psi, void* out, const ApplyPlan& P, hipStream_t s)
 {
+    if (use_table(H, P, nvec, elem_bytes(dtype))) {
+        if (dtype == SYK_C128) ensure_table<double>(H, H.table_d, s);
+        else ensure_table<float>(H, H.table_f, s);
+        timing_begin(s);
+        launch_table_any(H, dtype, nvec, real_of_col, psi, out, s);
+        timing_end(s);
+        return;
+    }
     const bool two = P.two_layouts != 0;
     if (two) {
         const size_t bytes = (size_t)std::min(nvec, kColsPerLaunch) * ((uint64_t)1 << H.M) * elem_bytes(dtype);

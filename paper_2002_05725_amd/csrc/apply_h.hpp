@@ -72,6 +72,7 @@ struct ApplyPlan {
     int rpt;         // tile rows per thread
     int xcd_remap;
     int two_layouts; // also run the masks that flip few rows of a tile on a bit-rotated copy
+    bool fixed_tile; // the tile was chosen by the caller
     int parts;       // > 1: the masks are split over this many workgroups per tile, whose sums a second kernel adds
     int nc;          // columns per workgroup where a launch's columns pair up by realisation (1 or 2)
 };

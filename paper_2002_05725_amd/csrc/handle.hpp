@@ -35,6 +35,8 @@ struct HamiltonianDev {
     mutable std::map<int, std::unique_ptr<ApplyTables>> apply_tables;
     // Rotated copies of psi and of the second layout's output (two-layout plans).
     mutable DevBuf rot_in, rot_out;
+    // Coefficients of every mask and row of small states, per element type (filled on first use).
+    mutable DevBuf table_d, table_f;
     // Partial sums of launches with their masks split over several workgroups per tile.
     mutable DevBuf parts;
     // The diagonal of H per realisation (FP64, [n_real][2^M]), filled on the

@@ -1,6 +1,8 @@
-"""apply_H of small states, whose masks are split over several workgroups per
-tile and summed by a second kernel, against the checker: one tile (N = 22), a
-few tiles, masks that flip only qubits above the tile (N = 34, 36), two row
+"""apply_H of small states against the checker.  Up to 2^12 rows and a few
+columns the product runs from a coefficient table (fewer rows than a
+workgroup's 16, the largest state, and blocks at which the table gives way);
+above, the masks are split over several workgroups per tile and summed by a
+second kernel: one tile (N = 22), a few tiles, masks that flip only qubits above the tile (N = 34, 36), two row
 layouts (N = 38), columns that do not pair up, and parity sectors."""
 import numpy as np
 import pytest
@@ -19,7 +21,7 @@ def _rel(a, b):
 
 
 @pytest.mark.parametrize("dtype", list(TOL))
-@pytest.mark.parametrize("N,nvec", [(22, 1), (24, 3), (26, 33), (34, 1), (36, 2), (38, 1)])
+@pytest.mark.parametrize("N,nvec", [(4, 1), (6, 3), (8, 2), (20, 10), (22, 70), (24, 1), (24, 3), (26, 33), (34, 1), (36, 2), (38, 1)])
 def test_split_product_matches_checker(N, nvec, dtype):
     Js = np.stack([inputs.couplings(N, 40 + r) for r in range(min(nvec, 2))])
     real = np.array([c % len(Js) for c in range(nvec)], dtype=np.int32)
@@ -37,7 +39,7 @@ def test_split_product_matches_checker(N, nvec, dtype):
     T.close()
 
 
-@pytest.mark.parametrize("N", [24, 36])
+@pytest.mark.parametrize("N", [6, 20, 24, 26, 36])
 def test_split_product_of_a_sector_matches_the_full_one(N):
     M = N // 2
     T = api.Terms(N, inputs.couplings(N, 3))
