@@ -11,6 +11,9 @@ the fastest is installed on the handle, and the choice is cached in a JSON file
 keyed by (device architecture, N, dtype, block width), so a later run installs
 it without timing.
 
+The library's automatic shape (which also has kernels of its own for small
+states and for tiles of 2^12 rows) is timed beside the candidates.
+
 All arithmetic runs in the library; this module only chooses among launch
 shapes that produce the same product (up to the order of FP64 row sums).
 """
@@ -98,6 +101,14 @@ def time_shape(terms: api.Terms, x: torch.Tensor, y: torch.Tensor, tile_bits: in
     return ms / n
 
 
+def _install(terms: api.Terms, entry: dict) -> None:
+    """Sets the entry's shape on the handle, or the automatic one if that was as fast."""
+    if entry.get("automatic_ms", float("inf")) <= entry["ms"]:
+        api.set_apply_tuning(terms, 0, 1, 0)
+    else:
+        api.set_apply_tuning(terms, entry["tile_bits"], entry["xcd_remap"], entry.get("cols_per_group", 1))
+
+
 def tune_apply(terms: api.Terms, dtype: torch.dtype = torch.complex128, nvec: int = 1, reps: int = 3,
                cache: str | None = DEFAULT_CACHE, shapes: list[tuple[int, int, int]] | None = None,
                use_cache: bool = True) -> dict:
@@ -105,7 +116,9 @@ def tune_apply(terms: api.Terms, dtype: torch.dtype = torch.complex128, nvec: in
     block of `nvec` columns (timed with every column in realisation 0, so
     that two-column shapes apply).  With use_cache and a cached entry for this
     key, installs that entry without timing.  Returns the chosen entry
-    {"tile_bits", "xcd_remap", "cols_per_group", "ms", "timed": [...]}."""
+    {"tile_bits", "xcd_remap", "cols_per_group", "ms", "timed": [...],
+    "automatic_ms"}; the library's automatic shape is installed instead where it
+    is at least as fast as the fastest candidate."""
     if dtype not in (torch.complex128, torch.complex64):
         raise ValueError("dtype must be complex128 or complex64")
     if nvec < 1 or reps < 1:
@@ -114,7 +127,7 @@ def tune_apply(terms: api.Terms, dtype: torch.dtype = torch.complex128, nvec: in
     if cache and use_cache:
         hit = read_cache(cache).get(key)
         if hit is not None:
-            api.set_apply_tuning(terms, hit["tile_bits"], hit["xcd_remap"], hit.get("cols_per_group", 1))
+            _install(terms, hit)
             return hit
     shape = (terms.dim,) if nvec == 1 else (nvec, terms.dim)
     g = torch.Generator(device="cuda").manual_seed(0)
@@ -124,10 +137,11 @@ def tune_apply(terms: api.Terms, dtype: torch.dtype = torch.complex128, nvec: in
     for tb, xr, nc in (shapes or candidates(terms.N, nvec)):
         timed.append({"tile_bits": tb, "xcd_remap": xr, "cols_per_group": nc,
                       "ms": time_shape(terms, x, y, tb, xr, reps, nc)})
-    del x, y
     best = dict(pick(timed))
     best["timed"] = timed
-    api.set_apply_tuning(terms, best["tile_bits"], best["xcd_remap"], best["cols_per_group"])
+    best["automatic_ms"] = time_shape(terms, x, y, 0, 1, reps, 0)
+    del x, y
+    _install(terms, best)
     if cache:
         write_cache(cache, key, best)
     return best

@@ -19,6 +19,7 @@
 // entries, lane index and sign, PAIR coefficients) is formed once and applied
 // to every column.  Up to 64 columns per launch.
 #include <algorithm>
+#include <cmath>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -55,6 +56,7 @@ struct KLayout {
     int n_parts;       // > 1: workgroup z sums only chunks part_chunk[z] .. part_chunk[z + 1] - 1 and its share of
                        // the far masks, into its own slice of the FP64 partial sums
     const uint32_t* __restrict__ part_chunk;
+    int n_tables;           // 16-row kernel: staged QUAD tables per realisation
     uint64_t part_stride;   // elements per slice: columns of the launch * dim
     int32_t real[kColsPerLaunch];  // realisation of each column of the launch
 };
@@ -897,6 +899,16 @@ void launch_k_apply(const ApplyPlan& P, const KTerms<R>& T, const QApplyChunk* c
     SYK_HIP(hipGetLastError());
 }
 
+// out = the sum of a split launch's slices (nothing otherwise)
+template <typename R>
+void sum_parts(const KLayout& L, const c128* parts, cplx<R>* out, hipStream_t s)
+{
+    if (L.n_parts <= 1) return;
+    const uint64_t n = L.part_stride;
+    hipLaunchKernelGGL(k_sum_parts<R>, dim3((uint32_t)((n + 31) / 32)), dim3(256), 0, s, parts, L.n_parts, n, out);
+    SYK_HIP(hipGetLastError());
+}
+
 template <typename R>
 void launch_t(const ApplyPlan& P, const KTerms<R>& T, const QApplyChunk* chunks, const QRec* rec, const KLayout& L,
               int ncols, int nc, const void* psi, void* out, c128* parts, hipStream_t s)
@@ -905,14 +917,10 @@ void launch_t(const ApplyPlan& P, const KTerms<R>& T, const QApplyChunk* chunks,
     auto* o = static_cast<cplx<R>*>(out);
     if (L.n_parts > 1) launch_k_apply<R, true>(P, T, chunks, rec, L, ncols, nc, in, o, parts, s);
     else launch_k_apply<R, false>(P, T, chunks, rec, L, ncols, nc, in, o, parts, s);
-    if (L.n_parts > 1) {
-        const uint64_t n = L.part_stride;
-        hipLaunchKernelGGL(k_sum_parts<R>, dim3((uint32_t)((n + 31) / 32)), dim3(256), 0, s, parts, L.n_parts, n, o);
-        SYK_HIP(hipGetLastError());
-    }
+    sum_parts<R>(L, parts, o, s);
 }
 
-constexpr int kSplitGroups = 1024, kMaxParts = 64;
+constexpr int kSplitGroups = 1024, kMaxParts = 64, kGroupSlots = 512;
 
 // About what a mask costs a workgroup, in single QUAD masks (a PAIR mask has
 // twice the arithmetic and reads its weights with scalar loads; one that flips
@@ -920,6 +928,26 @@ constexpr int kSplitGroups = 1024, kMaxParts = 64;
 // staged source tile cost.  Only used to cut the masks into parts of similar
 // cost.
 constexpr double kCostFlatPair = 5.0, kCostPair = 9.0, kCostDiag = 2.0, kCostChunk = 4.0, kCostTile = 8.0;
+
+#include "apply_groups.hpp"
+
+template <typename R>
+void launch_groups(const HamiltonianDev& H, const KTerms<R>& T, const HamiltonianDev::GroupTables& A, const KLayout& L, int ncols, const void* psi,
+                   void* out, c128* parts, hipStream_t s)
+{
+    auto* in = static_cast<const cplx<R>*>(psi);
+    auto* o = static_cast<cplx<R>*>(out);
+    const auto* ch = A.chunks.as<GroupChunk>();
+    const auto* gr = A.groups.as<GroupRec>();
+    const auto* tb = A.tables.as<cplx<R>>();
+    const auto* pt = (sizeof(R) == 8 ? H.pair_tab_d : H.pair_tab_f).as<cplx<R>>();
+    const auto* pr = A.pairs.as<PairRec>();
+    const dim3 grid(L.n_tiles, ncols, L.n_parts), block(256);
+    if (L.n_parts > 1) hipLaunchKernelGGL((k_apply_groups<R, true>), grid, block, 0, s, T, ch, gr, tb, pt, pr, L, in, o, parts);
+    else hipLaunchKernelGGL((k_apply_groups<R, false>), grid, block, 0, s, T, ch, gr, tb, pt, pr, L, in, o, parts);
+    SYK_HIP(hipGetLastError());
+    sum_parts<R>(L, parts, o, s);
+}
 
 // Chunks and class-sorted records of the apply kernel for tiles of 2^tile_bits
 // rows, 2^lane_bits threads and elements of esz bytes.  masks must be sorted by
@@ -1115,23 +1143,30 @@ void build_apply_tables(const std::vector<MaskRec>& masks_in, int tile_bits, int
     recs.push_back(QRec{});   // one record past the end: loads may run one ahead
 }
 
-// Chunk boundaries of n_parts contiguous parts of similar cost
-// (part_chunk[p] .. part_chunk[p + 1] - 1; parts may be empty).
-std::vector<uint32_t> part_bounds(const std::vector<QApplyChunk>& chunks, int n_parts)
+// Cost of every chunk (see above).
+std::vector<double> chunk_costs(const std::vector<QApplyChunk>& chunks)
 {
-    std::vector<double> sum(chunks.size() + 1, 0.0);
-    for (size_t g = 0; g < chunks.size(); ++g) {
-        const QApplyChunk& c = chunks[g];
+    std::vector<double> cost;
+    for (const QApplyChunk& c : chunks) {
         uint32_t n_flat = 0;
         for (int b = 0; b < 8; ++b) n_flat += (c.pcnt[b >> 2] >> (8 * (b & 3))) & 0xffu;
-        sum[g + 1] = sum[g] + c.n_quad + kCostFlatPair * n_flat + kCostPair * (c.n_pair - n_flat) + kCostDiag * c.n_diag +
-                     kCostChunk + (c.new_tile ? kCostTile : 0.0);
+        cost.push_back(c.n_quad + kCostFlatPair * n_flat + kCostPair * (c.n_pair - n_flat) + kCostDiag * c.n_diag +
+                       kCostChunk + (c.new_tile ? kCostTile : 0.0));
     }
-    std::vector<uint32_t> b(n_parts + 1, (uint32_t)chunks.size());
+    return cost;
+}
+
+// Chunk boundaries of n_parts contiguous parts of similar cost
+// (bounds p .. p + 1 - 1; parts may be empty).
+std::vector<uint32_t> part_bounds(const std::vector<double>& cost, int n_parts)
+{
+    std::vector<double> sum(cost.size() + 1, 0.0);
+    for (size_t g = 0; g < cost.size(); ++g) sum[g + 1] = sum[g] + cost[g];
+    std::vector<uint32_t> b(n_parts + 1, (uint32_t)cost.size());
     uint32_t g = 0;
     for (int p = 0; p < n_parts; ++p) {
         // the first chunk whose middle lies at or after the part's start
-        while (g < chunks.size() && 0.5 * (sum[g] + sum[g + 1]) < sum.back() * p / n_parts) ++g;
+        while (g < cost.size() && 0.5 * (sum[g] + sum[g + 1]) < sum.back() * p / n_parts) ++g;
         b[p] = g;
     }
     return b;
@@ -1210,6 +1245,87 @@ std::vector<KRec> build_krecs(const std::vector<MaskRec>& masks, const std::vect
 
 namespace {
 
+// The row layout of the 16-row kernel's second pass: the top kGroupTileBits
+// qubits become the low bits of a tile (a rotation by M - kGroupTileBits, so that
+// a tile's bits are neighbouring qubits at every M).  A QUAD mask runs there when
+// it flips more qubits above the natural tile than below the rotated one; where
+// the two tiles share qubits (M < 24) those count as the natural tile's, so that
+// all masks of a group, in either layout, go the same way.  M >= 16: the rotated
+// tile's k bits lie above the natural tile.
+std::vector<MaskRec> group_layout_masks(const std::vector<MaskRec>& masks, int M, bool two, int layout)
+{
+    const int rot = M - kGroupTileBits;
+    if (two && rot < kGroupKBits) throw Error(SYK_EINVAL, "apply_H groups: too few qubits for two layouts");
+    const uint32_t below = (1u << std::max(kGroupTileBits, rot)) - 1u;
+    std::vector<MaskRec> out;
+    for (const MaskRec& m : masks) {
+        const int out_a = __builtin_popcount(m.x >> kGroupTileBits);
+        const int out_b = __builtin_popcount(m.x & below);
+        const int in_b = two && (m.type_tab >> 28) == MASK_QUAD && out_b < out_a;
+        if (in_b != layout) continue;
+        out.push_back(layout == 0 ? m : rotate_mask(m, M, rot));
+    }
+    return out;
+}
+
+int group_tables_key(const ApplyPlan& P, uint32_t esz, int layout)
+{
+    return (((int)esz * 2 + P.two_layouts) * 2 + layout) * 256 + P.parts;
+}
+
+const HamiltonianDev::GroupTables& group_tables_for(const HamiltonianDev& H, const ApplyPlan& P, uint32_t esz, int layout)
+{
+    const int key = group_tables_key(P, esz, layout);
+    auto it = H.group_tables.find(key);
+    if (it == H.group_tables.end()) {
+        const std::vector<MaskRec> masks = group_layout_masks(*H.host_masks, H.M, P.two_layouts != 0, layout);
+        // parts of a split launch: chunks of at most half a part's share, so that the parts come out even
+        const double cost = (double)masks.size() + 4.0 * H.M * H.M / 2;
+        const GroupTables G = build_group_tables(masks, esz, P.parts > 1 ? std::max(6.0, 0.5 * cost / P.parts) : 0.0);
+        std::unique_ptr<HamiltonianDev::GroupTables> t(new HamiltonianDev::GroupTables());
+        t->n_chunks = (int)G.chunks.size();
+        t->n_far = (int)G.far.size();
+        auto up = [](DevBuf& b, const auto& v) {
+            const size_t n = v.size() * sizeof(v[0]);
+            b.ensure(std::max<size_t>(n, 64));
+            if (n) SYK_HIP(hipMemcpy(b.p, v.data(), n, hipMemcpyHostToDevice));
+        };
+        up(t->chunks, G.chunks);
+        up(t->groups, G.groups);
+        up(t->pairs, G.pairs);
+        t->n_tables = (int)G.tabs.size();
+        // the QUAD tables in staging order, and the PAIR masks' (once per handle and
+        // element type); finished before this returns, as later calls may come on other streams
+        DevBuf idx;
+        up(idx, G.tabs);
+        const uint32_t n16 = (uint32_t)G.tabs.size() * 16u;
+        t->tables.ensure(std::max<size_t>((size_t)n16 * H.n_real * esz, 64));
+        const dim3 og((n16 + 255) / 256, (uint32_t)H.n_real), pg((uint32_t)H.host_masks->size(), (uint32_t)H.n_real);
+        size_t n_pairs = 0;
+        for (const MaskRec& m : *H.host_masks) n_pairs += (m.type_tab >> 28) == MASK_PAIR;
+        DevBuf& pt = esz == 16 ? H.pair_tab_d : H.pair_tab_f;
+        const bool need = pt.p == nullptr;
+        if (need) pt.ensure(std::max<size_t>(n_pairs * H.n_real * pair_table_size(H.M) * esz, 64));
+        auto build = [&](auto zero, const auto* tab4) {
+            typedef decltype(zero) R;
+            if (n16)
+                hipLaunchKernelGGL(k_order_tables<R>, og, dim3(256), 0, 0, tab4, idx.as<uint32_t>(), t->n_tables, H.n_real,
+                                   t->tables.as<cplx<R>>());
+            if (need)
+                hipLaunchKernelGGL(k_pair_tables<R>, pg, dim3(256), 0, 0, H.masks, H.phi2_d, H.w2_d, H.n_real, H.M,
+                                   pt.as<cplx<R>>());
+        };
+        if (esz == 16) build(0.0, H.tab4_d);
+        else build(0.0f, H.tab4_f);
+        SYK_HIP(hipGetLastError());
+        SYK_HIP(hipStreamSynchronize(0));
+        up(t->far, G.far);
+        if (P.parts > 1) up(t->part_chunk, part_bounds(G.cost, P.parts));
+        it = H.group_tables.emplace(key, std::move(t)).first;
+    }
+    return *it->second;
+}
+
 int apply_tables_key(const ApplyPlan& P, uint32_t esz, int layout)
 {
     return ((((P.tile_bits * 16 + P.lb) * 32 + (int)esz) * 2 + P.two_layouts) * 2 + layout) * 256 + P.parts;
@@ -1241,7 +1357,7 @@ const HamiltonianDev::ApplyTables& apply_tables_for(const HamiltonianDev& H, con
             SYK_HIP(hipMemcpy(t->far.p, far.data(), far.size() * sizeof(FarRec), hipMemcpyHostToDevice));
         }
         if (P.parts > 1) {
-            const std::vector<uint32_t> pb = part_bounds(ch, P.parts);
+            const std::vector<uint32_t> pb = part_bounds(chunk_costs(ch), P.parts);
             t->part_chunk.ensure(pb.size() * sizeof(uint32_t));
             SYK_HIP(hipMemcpy(t->part_chunk.p, pb.data(), pb.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
         }
@@ -1254,7 +1370,7 @@ const HamiltonianDev::ApplyTables& apply_tables_for(const HamiltonianDev& H, con
 
 }  // namespace
 
-ApplyPlan plan_apply(int M, int nvec, syk_dtype dtype, const ApplyTuning* tune)
+ApplyPlan plan_apply(int M, int nvec, syk_dtype dtype, const ApplyTuning* tune, bool allow_groups)
 {
     ApplyPlan P{};
     P.slices = (nvec + kColsPerLaunch - 1) / kColsPerLaunch;
@@ -1279,6 +1395,28 @@ ApplyPlan plan_apply(int M, int nvec, syk_dtype dtype, const ApplyTuning* tune)
     }
     // 8 lane bits; a thread owns 2^(tile_bits - 8) rows, at most 8
     if (tb > kLaneBits + kMaxKBits) throw Error(SYK_EINVAL, "apply_H: tile_bits above 11");
+    // From 2^13 rows on the 16-row kernel with tiles of 2^12 rows (one complex128
+    // column, us, 8 rows -> 16: N=26 20 -> 18, N=32 62 -> 48, N=36 254 -> 218, N=44 7176 ->
+    // 5700; complex64 N=32 47 -> 42, N=44 4613 -> 4120; an exception in plan_of_call).  Its
+    // split fills the 512 workgroups the chip holds (two per CU): the parts that
+    // cost the fewest rounds of them, each part weighed with the 128 KiB its sums
+    // write and read per workgroup (N=32: 48 us with 32 parts, 61 with 64; seven
+    // columns: 246 with nine parts, 279 with five, whose last round is part-full).
+    P.groups = allow_groups && !P.fixed_tile && M > kGroupTileBits;
+    if (P.groups) {
+        tb = kGroupTileBits;
+        const int64_t wg = ((int64_t)1 << (M - tb)) * std::min(nvec, kColsPerLaunch);
+        const double n_masks = M * (M - 1) * (double)(M - 2) * (M - 3) / 24.0 + M * (M - 1) / 2.0;
+        double best = 1e300;
+        P.parts = 1;
+        for (int p = 1; p <= kMaxParts && (p == 1 || p * wg <= kSplitGroups); ++p) {
+            const double score = (double)((wg * p + kGroupSlots - 1) / kGroupSlots) / p + 0.13 * wg * (p - 1) / n_masks;
+            if (score < best) {
+                best = score;
+                P.parts = p;
+            }
+        }
+    }
     P.tile_bits = tb;
     P.lb = std::min(tb, kLaneBits);
     P.nt = 1 << P.lb;
@@ -1291,6 +1429,7 @@ ApplyPlan plan_apply(int M, int nvec, syk_dtype dtype, const ApplyTuning* tune)
     // both; complex128 would drop to two waves per SIMD and gains nothing.
     const bool explicit_cols = tune && tune->cols > 0;
     P.nc = explicit_cols ? tune->cols : (dtype == SYK_C64 ? 2 : 1);
+    if (P.groups) P.nc = 1;
     if (P.nc == 2 && P.rpt < 4) {
         if (explicit_cols && tune->tile_bits > 0)
             throw Error(SYK_EINVAL, "apply_H: two columns per workgroup need tile_bits >= 10");
@@ -1302,7 +1441,10 @@ ApplyPlan plan_apply(int M, int nvec, syk_dtype dtype, const ApplyTuning* tune)
     // short enough that the second layout's launches (two transposes, another
     // product and sum) weigh more: from C(8,4) on (N=36: 261 us with one layout,
     // 283 with two; N=38: 583 both; N=34, where C(6,4): 120 with one, 146 with two).
-    P.two_layouts = (M - tb >= (P.parts > 1 ? 8 : 7) && tb >= 8) ? 1 : 0;
+    // The 16-row kernel unsplit: from C(6,4) on (64 complex64 columns at N=36: 7.29 ms
+    // with two layouts, 7.45 with one).
+    P.two_layouts = (M - tb >= (P.parts > 1 ? 8 : P.groups ? 6 : 7) && tb >= 8) ? 1 : 0;
+    P.rot = P.groups ? M - tb : tb;
     return P;
 }
 
@@ -1311,6 +1453,21 @@ void launch_apply_impl(const HamiltonianDev& H, syk_dtype dtype, int nvec, const
                        const void* psi, void* out, const ApplyPlan& P, hipStream_t s, void* rot_in, void* rot_out,
                        void* parts, bool timed);
 }  // namespace
+
+// The plan of one call: complex64 blocks whose columns pair up by realisation,
+// 2^17 to 2^19 rows and enough columns to fill the chip, run two columns per
+// workgroup at 8 rows per thread (N=36, 32 columns: 3.65 ms against 3.75-3.97 with
+// the 16-row kernel, 64 columns: 7.30 against 7.42-7.50; N=38, 64 columns: 17.9
+// against 18.1).  Below, the 16-row kernel is faster (N=32: 1.23 against 1.50),
+// and from 2^20 rows on again (N=40, 64 columns: 43.4 against 44.3).
+static ApplyPlan plan_of_call(const HamiltonianDev& H, const ApplyPlan& P, syk_dtype dtype, int nvec, const int32_t* real)
+{
+    if (!P.groups || P.parts > 1 || dtype != SYK_C64 || H.M < 17 || H.M > 19 || nvec % 2 != 0) return P;
+    for (int c = 0; real && c < nvec; c += 2)
+        if (real[c] != real[c + 1]) return P;
+    const ApplyPlan Q = plan_apply(H.M, nvec, dtype, nullptr, false);
+    return Q.parts == 1 && Q.nc == 2 ? Q : P;
+}
 
 // Bytes of the partial sums of a split launch (FP64 for both state types).
 static size_t parts_bytes(const ApplyPlan& P, int nvec, uint64_t dim)
@@ -1342,9 +1499,10 @@ void* noalloc_scratch_ptr(int device)
 }
 
 void launch_apply_h_noalloc(const HamiltonianDev& H, int device, syk_dtype dtype, int nvec,
-                            const int32_t* real_of_col, const void* psi, void* out, const ApplyPlan& P,
+                            const int32_t* real_of_col, const void* psi, void* out, const ApplyPlan& plan,
                             hipStream_t s)
 {
+    const ApplyPlan P = plan_of_call(H, plan, dtype, nvec, real_of_col);
     const size_t esz = elem_bytes(dtype);
     const uint64_t dim = (uint64_t)1 << H.M;
     if (use_table(H, P, nvec, esz)) {
@@ -1361,7 +1519,10 @@ void launch_apply_h_noalloc(const HamiltonianDev& H, int device, syk_dtype dtype
                                     " bytes of scratch, above the maximum of " +
                                     std::to_string(kNoAllocScratchBytes));
     // everything the handle builds on first use must exist already
-    auto have = [&](int layout) { return H.apply_tables.count(apply_tables_key(P, (uint32_t)esz, layout)) != 0; };
+    auto have = [&](int layout) {
+        return P.groups ? H.group_tables.count(group_tables_key(P, (uint32_t)esz, layout)) != 0
+                        : H.apply_tables.count(apply_tables_key(P, (uint32_t)esz, layout)) != 0;
+    };
     if (!H.diag_ready || !have(0) || (P.two_layouts && !have(1)))
         throw Error(SYK_EINVAL, "apply_H_noalloc: the handle has no tables for this dtype and block width yet "
                                 "(call syk_apply_H once with them first)");
@@ -1371,8 +1532,9 @@ void launch_apply_h_noalloc(const HamiltonianDev& H, int device, syk_dtype dtype
 }
 
 void launch_apply_h(const HamiltonianDev& H, syk_dtype dtype, int nvec, const int32_t* real_of_col,
-                    const void* psi, void* out, const ApplyPlan& P, hipStream_t s)
+                    const void* psi, void* out, const ApplyPlan& plan, hipStream_t s)
 {
+    const ApplyPlan P = plan_of_call(H, plan, dtype, nvec, real_of_col);
     if (use_table(H, P, nvec, elem_bytes(dtype))) {
         if (dtype == SYK_C128) ensure_table<double>(H, H.table_d, s);
         else ensure_table<float>(H, H.table_f, s);
@@ -1402,16 +1564,22 @@ void launch_apply_impl(const HamiltonianDev& H, syk_dtype dtype, int nvec, const
                        void* parts, bool timed)
 {
     const int M = H.M;
-    if (P.lb > kLaneBits || (P.rpt > 1 && P.lb != kLaneBits) || P.nt != (1 << P.lb) ||
+    if (P.groups ? P.tile_bits != kGroupTileBits || P.nt != 256 || P.rpt != kGroupRows || P.tile_bits > M :
+        P.lb > kLaneBits || (P.rpt > 1 && P.lb != kLaneBits) || P.nt != (1 << P.lb) ||
         (P.nc != 1 && (P.nc != 2 || P.rpt < 4)) ||
         (P.rpt << P.lb) != (1 << P.tile_bits) || P.tile_bits > M ||
         (P.two_layouts && (P.tile_bits < 5 || M - P.tile_bits < 5)))
         throw Error(SYK_EINVAL, "apply_H: inconsistent launch shape");
+    if (P.two_layouts && (P.rot < 5 || M - P.rot < 5)) throw Error(SYK_EINVAL, "apply_H: inconsistent launch shape");
     const size_t esz = elem_bytes(dtype);
     const uint64_t dim = (uint64_t)1 << M;
-    const HamiltonianDev::ApplyTables& A = apply_tables_for(H, P, (uint32_t)esz, 0);
-    const HamiltonianDev::ApplyTables* B = P.two_layouts ? &apply_tables_for(H, P, (uint32_t)esz, 1) : nullptr;
-    if (B && (!rot_in || !rot_out)) throw Error(SYK_EINVAL, "apply_H: no buffers for the rotated layout");
+    const bool two = P.two_layouts != 0;
+    // the tables of both layouts exist before the first launch
+    for (int l = 0; l <= P.two_layouts; ++l) {
+        if (P.groups) (void)group_tables_for(H, P, (uint32_t)esz, l);
+        else (void)apply_tables_for(H, P, (uint32_t)esz, l);
+    }
+    if (two && (!rot_in || !rot_out)) throw Error(SYK_EINVAL, "apply_H: no buffers for the rotated layout");
     if (P.parts > 1 && !parts) throw Error(SYK_EINVAL, "apply_H: no buffer for the partial sums");
     if (timed) timing_begin(s);
     for (int sl = 0; sl < P.slices; ++sl) {
@@ -1432,31 +1600,41 @@ void launch_apply_impl(const HamiltonianDev& H, syk_dtype dtype, int nvec, const
             if (L.real[c] != L.real[c + 1]) nc = 1;
         const char* in_c = static_cast<const char*>(psi) + (size_t)col0 * dim * esz;
         char* out_c = static_cast<char*>(out) + (size_t)col0 * dim * esz;
-        auto run = [&](const HamiltonianDev::ApplyTables& Tb, const void* src, void* dst) {
-            L.far = Tb.far.as<FarRec>();
-            L.n_far = Tb.n_far;
-            L.n_chunks = Tb.n_chunks;
+        auto run = [&](int layout, const void* src, void* dst) {
             L.n_parts = P.parts;
-            L.part_chunk = Tb.part_chunk.as<uint32_t>();
             L.part_stride = (uint64_t)ncols * dim;
-            const auto* ch = Tb.chunks.as<QApplyChunk>();
-            const auto* rc = Tb.recs.as<QRec>();
-            if (dtype == SYK_C128) {
-                KTerms<double> T{H.tab4_d, H.qinfo, H.phi2_d, H.w2_d, H.diag.as<double>(), H.n_real, M};
-                launch_t<double>(P, T, ch, rc, L, ncols, nc, src, dst, static_cast<c128*>(parts), s);
-            } else {
-                KTerms<float> T{H.tab4_f, H.qinfo, H.phi2_f, H.w2_f, H.diag.as<double>(), H.n_real, M};
-                launch_t<float>(P, T, ch, rc, L, ncols, nc, src, dst, static_cast<c128*>(parts), s);
-            }
+            c128* pt = static_cast<c128*>(parts);
+            auto launch = [&](auto zero, const auto* tab4, const auto* phi2, const auto* w2) {
+                typedef decltype(zero) R;
+                const KTerms<R> T{tab4, H.qinfo, phi2, w2, H.diag.as<double>(), H.n_real, M};
+                if (P.groups) {
+                    const HamiltonianDev::GroupTables& Tb = group_tables_for(H, P, (uint32_t)esz, layout);
+                    L.far = Tb.far.as<FarRec>();
+                    L.n_far = Tb.n_far;
+                    L.n_chunks = Tb.n_chunks;
+                    L.n_tables = Tb.n_tables;
+                    L.part_chunk = Tb.part_chunk.as<uint32_t>();
+                    launch_groups<R>(H, T, Tb, L, ncols, src, dst, pt, s);
+                } else {
+                    const HamiltonianDev::ApplyTables& Tb = apply_tables_for(H, P, (uint32_t)esz, layout);
+                    L.far = Tb.far.as<FarRec>();
+                    L.n_far = Tb.n_far;
+                    L.n_chunks = Tb.n_chunks;
+                    L.part_chunk = Tb.part_chunk.as<uint32_t>();
+                    launch_t<R>(P, T, Tb.chunks.as<QApplyChunk>(), Tb.recs.as<QRec>(), L, ncols, nc, src, dst, pt, s);
+                }
+            };
+            if (dtype == SYK_C128) launch(0.0, H.tab4_d, H.phi2_d, H.w2_d);
+            else launch(0.0f, H.tab4_f, H.phi2_f, H.w2_f);
         };
-        if (B) {
+        if (two) {
             // rows r -> rotate_bits(r): a [2^(M-s)] x [2^s] transpose
-            launch_transpose(dtype, in_c, rot_in, M - P.tile_bits, P.tile_bits, ncols, dim, false, s);
-            run(*B, rot_in, rot_out);
-            run(A, in_c, out_c);
-            launch_transpose(dtype, rot_out, out_c, P.tile_bits, M - P.tile_bits, ncols, dim, true, s);
+            launch_transpose(dtype, in_c, rot_in, M - P.rot, P.rot, ncols, dim, false, s);
+            run(1, rot_in, rot_out);
+            run(0, in_c, out_c);
+            launch_transpose(dtype, rot_out, out_c, P.rot, M - P.rot, ncols, dim, true, s);
         } else {
-            run(A, in_c, out_c);
+            run(0, in_c, out_c);
         }
     }
     if (timed) timing_end(s);

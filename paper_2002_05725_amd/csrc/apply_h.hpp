@@ -74,10 +74,13 @@ struct ApplyPlan {
     int two_layouts; // also run the masks that flip few rows of a tile on a bit-rotated copy
     bool fixed_tile; // the tile was chosen by the caller
     int parts;       // > 1: the masks are split over this many workgroups per tile, whose sums a second kernel adds
+    int groups;      // the 16-row kernel with every QUAD mask in a group (tiles of 2^12 rows)
+    int rot;         // two layouts: the second one's row bits are rotated right by this many
     int nc;          // columns per workgroup where a launch's columns pair up by realisation (1 or 2)
 };
 
-ApplyPlan plan_apply(int M, int nvec, syk_dtype dtype, const ApplyTuning* tune);
+// allow_groups: the 16-row kernel may be chosen.
+ApplyPlan plan_apply(int M, int nvec, syk_dtype dtype, const ApplyTuning* tune, bool allow_groups = true);
 
 // The plan for a handle's tables of M qubits, honouring its
 // syk_set_apply_tuning settings.

@@ -33,6 +33,13 @@ struct HamiltonianDev {
         int n_chunks = 0, n_far = 0;
     };
     mutable std::map<int, std::unique_ptr<ApplyTables>> apply_tables;
+    // Tables of the 16-row kernel, per element size, layout and split.
+    struct GroupTables {
+        DevBuf chunks, groups, tables, pairs, far, part_chunk;
+        int n_chunks = 0, n_far = 0, n_tables = 0;
+    };
+    mutable DevBuf pair_tab_d, pair_tab_f;   // its PAIR tables per element type
+    mutable std::map<int, std::unique_ptr<GroupTables>> group_tables;
     // Rotated copies of psi and of the second layout's output (two-layout plans).
     mutable DevBuf rot_in, rot_out;
     // Coefficients of every mask and row of small states, per element type (filled on first use).
