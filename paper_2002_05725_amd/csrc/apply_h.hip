@@ -1531,13 +1531,19 @@ void launch_apply_h_noalloc(const HamiltonianDev& H, int device, syk_dtype dtype
                       part ? sp + rot : nullptr, false);
 }
 
+const void* coefficient_table(const HamiltonianDev& H, const ApplyPlan& P, syk_dtype dtype, int nvec, hipStream_t s)
+{
+    if (!use_table(H, P, nvec, elem_bytes(dtype))) return nullptr;
+    if (dtype == SYK_C128) ensure_table<double>(H, H.table_d, s);
+    else ensure_table<float>(H, H.table_f, s);
+    return (dtype == SYK_C128 ? H.table_d : H.table_f).p;
+}
+
 void launch_apply_h(const HamiltonianDev& H, syk_dtype dtype, int nvec, const int32_t* real_of_col,
                     const void* psi, void* out, const ApplyPlan& plan, hipStream_t s)
 {
     const ApplyPlan P = plan_of_call(H, plan, dtype, nvec, real_of_col);
-    if (use_table(H, P, nvec, elem_bytes(dtype))) {
-        if (dtype == SYK_C128) ensure_table<double>(H, H.table_d, s);
-        else ensure_table<float>(H, H.table_f, s);
+    if (coefficient_table(H, P, dtype, nvec, s)) {
         timing_begin(s);
         launch_table_any(H, dtype, nvec, real_of_col, psi, out, s);
         timing_end(s);

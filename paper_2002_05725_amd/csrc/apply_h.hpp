@@ -110,6 +110,10 @@ MaskRec rotate_mask(const MaskRec& m, int M, int tb);
 void launch_transpose(syk_dtype dtype, const void* src, void* dst, int log_h, int log_w, int ncols, uint64_t dim,
                       bool add, hipStream_t s);
 
+// The table of D_x(r) over every mask and row that products of this plan run from
+// (small states; built on first use), or NULL: [realisation][block of 16 rows][mask][16].
+const void* coefficient_table(const HamiltonianDev& H, const ApplyPlan& P, syk_dtype dtype, int nvec, hipStream_t s);
+
 // out = H psi for nvec columns stored one after another; real_of_col: host array or NULL.
 void launch_apply_h(const HamiltonianDev& H, syk_dtype dtype, int nvec, const int32_t* real_of_col,
                     const void* psi, void* out, const ApplyPlan& P, hipStream_t s);

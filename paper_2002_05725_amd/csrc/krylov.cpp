@@ -5,12 +5,14 @@
 // Gram-Schmidt; inner products are FP64 on the device, T (tridiagonal QR for
 // its eigen-decomposition) and its exponential are FP64 on the host.  Up to 16 basis vectors the first pass's update and
 // the second pass's projection share one sweep over the basis (states of at
-// most 2048 rows do the whole iteration after the product in one launch).  The
+// most 2048 rows do the whole iteration after the product in one launch, of at
+// most 256 rows the whole build).  The
 // projections, alpha, beta and the invariant-subspace test stay on the device
 // for the whole build (no host round trip per iteration); the last iteration
 // writes them to pinned host memory, which the host reads after one
 // synchronisation.
 #include "krylov.hpp"
+#include "timing.hpp"
 #include "tridiag_eig.hpp"
 
 #include <algorithm>
@@ -54,10 +56,19 @@ LanczosBasis lanczos_build(BlockCtx& c, const void* psi, int m)
     void* w = c.h.ws.get("krylov_w", vb);
     char* V = L.V;
 
-    const LanczosScalars z = ops.lanczos_begin(psi, V, m);
-    for (int j = 0; j < m; ++j) {
-        c.apply_H(V + (size_t)j * vb, w);
-        ops.lanczos_step(w, V, j, m, z);
+    LanczosScalars z;
+    const int n_masks = (int)c.Hact->host_masks->size();
+    // (with kernel timing on, every product is a launch of its own)
+    const void* table = ops.one_launch_lanczos(m, n_masks) && !timing_enabled()
+                            ? coefficient_table(*c.Hact, c.plan, c.dtype, B, c.stream) : nullptr;
+    if (table) {
+        z = ops.lanczos_build(psi, V, m, table, c.Hact->masks, n_masks, c.real_of_col);
+    } else {
+        z = ops.lanczos_begin(psi, V, m);
+        for (int j = 0; j < m; ++j) {
+            c.apply_H(V + (size_t)j * vb, w);
+            ops.lanczos_step(w, V, j, m, z);
+        }
     }
     ops.synchronize();
     const size_t nB = (size_t)B;

@@ -451,14 +451,24 @@ __global__ void __launch_bounds__(kSmallThreads) k_lanczos_small(const cplx<R>* 
     for (int pass = 0; pass < 2; ++pass) {
         for (int k = wave; k < K; k += kSmallThreads / 64) {
             const cplx<R>* v = Vc + k * vstride;
-            double ar = 0.0, ai = 0.0;
-#pragma unroll 8
-            for (int r = lane; r < D; r += 64) {
+            // four running sums per lane: short chains of rounding errors
+            double a4[4] = {0.0, 0.0, 0.0, 0.0}, b4[4] = {0.0, 0.0, 0.0, 0.0};
+            auto add = [&](int r, int u) {
                 const cplx<R> x = v[r], y = ws[r];
                 const double vr = x.re, vi = x.im, br = y.re, bi = y.im;
-                ar += vr * br + vi * bi;
-                ai += vr * bi - vi * br;
+                a4[u] += vr * br + vi * bi;
+                b4[u] += vr * bi - vi * br;
+            };
+            if (D >= 256) {   // D is a power of two
+#pragma unroll 2
+                for (int r = lane; r < D; r += 256) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) add(r + 64 * u, u);
+                }
+            } else {
+                for (int r = lane; r < D; r += 64) add(r, 0);
             }
+            double ar = (a4[0] + a4[1]) + (a4[2] + a4[3]), ai = (b4[0] + b4[1]) + (b4[2] + b4[3]);
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) {
                 ar += __shfl_xor(ar, off, 64);
@@ -509,6 +519,148 @@ __global__ void __launch_bounds__(kSmallThreads) k_lanczos_small(const cplx<R>* 
         o.im = (R)(f * (double)x.im);
         vn[r] = o;
     }
+}
+
+// States of at most kOneRows rows: a whole Lanczos build in one launch, one
+// workgroup of 16 waves per column, with the basis in LDS and the product from the
+// handle's coefficient table ([realisation][row block][mask][16], apply_h.hip).
+// Two launches per iteration cost ~15 us whatever they did (G(t) at N=16 in one
+// sector: 15.2 ms of which the arithmetic is well under one); here an iteration is
+// bound by reading the table from L2 by one CU (0.4 MB at 256 rows) and by the
+// barriers between its six steps.
+constexpr int kOneRows = 256, kOneBasis = 8192, kOneMasks = 512, kOneColumns = 64, kOneMaxM = 128;
+
+struct OneColumns {
+    int32_t real[kOneColumns];
+};
+
+template <typename R>
+__global__ void __launch_bounds__(kSmallThreads) k_lanczos_build(const cplx<R>* __restrict__ psi, cplx<R>* V,
+                                                                 int64_t vstride, int m, Shape S,
+                                                                 const cplx<R>* __restrict__ table,
+                                                                 const MaskRec* __restrict__ masks, int n_masks,
+                                                                 OneColumns C, LanczosScalars z)
+{
+    constexpr int kW = kSmallThreads / 64;
+    __shared__ cplx<R> vs[kOneBasis];          // V_k at k * D
+    __shared__ cplx<R> ws[kOneRows];
+    __shared__ c128 part[kSmallThreads];       // product: partial sums per row
+    __shared__ double cs[2][2 * kOneMaxM];     // the projections of the two passes
+    __shared__ double red[kW];
+    __shared__ uint32_t xs[kOneMasks];
+    const int c = blockIdx.x, D = (int)S.D;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int64_t col = (int64_t)c * D;
+    const int nblk = (D + 15) / 16;
+    // row of this thread in the product, and its group of masks
+    const int r = t & (D - 1), group = t / D, groups = kSmallThreads / D;
+    const cplx<R>* tab = table + ((int64_t)C.real[c] * nblk + (r >> 4)) * n_masks * 16 + (r & 15);
+    for (int i = t; i < n_masks; i += kSmallThreads) xs[i] = masks[i].x;
+    // sum of one double per thread over the workgroup, in a fixed order
+    auto block_add = [&](double v) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        __syncthreads();
+        if (lane == 0) red[wave] = v;
+        __syncthreads();
+        double o = 0.0;
+        for (int i = 0; i < kW; ++i) o += red[i];
+        return o;
+    };
+    double n2 = 0.0;
+    if (t < D) {
+        const cplx<R> v = psi[col + t];
+        ws[t] = v;
+        n2 = (double)v.re * v.re + (double)v.im * v.im;
+    }
+    double f = lanczos_start(z, block_add(n2), m, c, t == 0);
+    for (int j = 0;; ++j) {
+        // V_j = f w, in LDS and for the combination
+        if (t < D) {
+            cplx<R> o;
+            o.re = (R)(f * (double)ws[t].re);
+            o.im = (R)(f * (double)ws[t].im);
+            vs[j * D + t] = o;
+            V[j * vstride + col + t] = o;
+        }
+        __syncthreads();
+        double ar = 0.0, ai = 0.0;
+#pragma unroll 8
+        for (int k = group; k < n_masks; k += groups) {
+            const cplx<R> d = tab[(int64_t)k * 16];
+            const cplx<R> v = vs[j * D + (r ^ (int)xs[k])];
+            const double dr = d.re, di = d.im, vr = v.re, vi = v.im;
+            ar = fma(dr, vr, ar);
+            ar = fma(-di, vi, ar);
+            ai = fma(dr, vi, ai);
+            ai = fma(di, vr, ai);
+        }
+        // lanes of a wave that hold the same row, then the waves in order
+        for (int off = D; off < 64; off <<= 1) {
+            ar += __shfl_xor(ar, off, 64);
+            ai += __shfl_xor(ai, off, 64);
+        }
+        part[t] = c128{ar, ai};
+        __syncthreads();
+        if (t < D) {
+            const int step = D < 64 ? 64 : D;
+            double sr = 0.0, si = 0.0;
+            for (int u = t; u < kSmallThreads; u += step) {
+                sr += part[u].re;
+                si += part[u].im;
+            }
+            cplx<R> o;
+            o.re = (R)sr;
+            o.im = (R)si;
+            ws[t] = o;
+        }
+        __syncthreads();
+        const int K = j + 1;
+        double nrm = 0.0;
+        for (int pass = 0; pass < 2; ++pass) {
+            for (int k = wave; k < K; k += kW) {
+                double br = 0.0, bi = 0.0;
+                for (int q = lane; q < D; q += 64) {
+                    const cplx<R> x = vs[k * D + q], y = ws[q];
+                    const double vr = x.re, vi = x.im, wr = y.re, wi = y.im;
+                    br += vr * wr + vi * wi;
+                    bi += vr * wi - vi * wr;
+                }
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) {
+                    br += __shfl_xor(br, off, 64);
+                    bi += __shfl_xor(bi, off, 64);
+                }
+                if (lane == 0) {
+                    cs[pass][2 * k] = br;
+                    cs[pass][2 * k + 1] = bi;
+                }
+            }
+            __syncthreads();
+            if (t < D) {
+                const cplx<R> b = ws[t];
+                double xr = b.re, xi = b.im;
+#pragma unroll 4
+                for (int k = 0; k < K; ++k) {
+                    const cplx<R> x = vs[k * D + t];
+                    const double cr = cs[pass][2 * k], ci = cs[pass][2 * k + 1];
+                    xr -= cr * x.re - ci * x.im;
+                    xi -= cr * x.im + ci * x.re;
+                }
+                cplx<R> o;
+                o.re = (R)xr;
+                o.im = (R)xi;
+                ws[t] = o;
+                const double orr = o.re, oi = o.im;
+                if (pass == 1) nrm = orr * orr + oi * oi;
+            }
+            __syncthreads();
+        }
+        f = lanczos_scalars(z, cs[0][2 * j] + cs[1][2 * j], block_add(nrm), j, m, S.B, c, t == 0);
+        __syncthreads();   // the scalars stored above are read by the next iteration
+        if (j == m - 1) break;
+    }
+    lanczos_publish(z, m, S.B, c, t, kSmallThreads);
 }
 
 // Coefficients of a combination for one column, passed with the launch.
@@ -709,7 +861,33 @@ std::vector<double> VecOps::norm2(const void* a)
 
 bool VecOps::small_lanczos(int m) const { return dim_ <= kSmallRows && m <= kSmallMaxM; }
 
-LanczosScalars VecOps::lanczos_begin(const void* psi, void* V, int m)
+bool VecOps::one_launch_lanczos(int m, int n_masks) const
+{
+    return dim_ <= kOneRows && (int64_t)m * dim_ <= kOneBasis && m <= kOneMaxM && n_masks <= kOneMasks &&
+           nvec_ <= kOneColumns;
+}
+
+LanczosScalars VecOps::lanczos_build(const void* psi, void* V, int m, const void* table, const MaskRec* masks, int n_masks,
+                                     const int32_t* real_of_col)
+{
+    if (!one_launch_lanczos(m, n_masks)) throw Error(SYK_EINVAL, "lanczos_build: unsupported size");
+    const LanczosScalars z = lanczos_arrays(m);
+    OneColumns C{};
+    for (int c = 0; c < nvec_; ++c) C.real[c] = real_of_col ? real_of_col[c] : 0;
+    Shape S{dim_, nvec_};
+    const dim3 g(nvec_), b(kSmallThreads);
+    const int64_t vs = dim_ * nvec_;
+    if (dt_ == SYK_C128)
+        hipLaunchKernelGGL(k_lanczos_build<double>, g, b, 0, s_, (const c128*)psi, (c128*)V, vs, m, S, (const c128*)table,
+                           masks, n_masks, C, z);
+    else
+        hipLaunchKernelGGL(k_lanczos_build<float>, g, b, 0, s_, (const c64*)psi, (c64*)V, vs, m, S, (const c64*)table,
+                           masks, n_masks, C, z);
+    SYK_HIP(hipGetLastError());
+    return z;
+}
+
+LanczosScalars VecOps::lanczos_arrays(int m)
 {
     const size_t B = (size_t)nvec_, mB = (size_t)m * B;
     double* d = (double*)h_.ws.get("lz_dbl", (3 * mB + 2 * B) * sizeof(double));
@@ -727,6 +905,12 @@ LanczosScalars VecOps::lanczos_begin(const void* psi, void* V, int m)
     z.h_nrm = h + 2 * mB;
     z.h_kdim = (int*)(h + 2 * mB + B);
     z.h_flag = z.h_kdim + B;
+    return z;
+}
+
+LanczosScalars VecOps::lanczos_begin(const void* psi, void* V, int m)
+{
+    const LanczosScalars z = lanczos_arrays(m);
     Shape S{dim_, nvec_};
     const Sums n = dots(psi, 0, 1, psi, "gs_n");
     const dim3 g = grid_of(S, false);

@@ -47,6 +47,11 @@ public:
     std::vector<double> norm2(const void* a);
     // V_0 = psi / ||psi|| and the scalars of a Lanczos build of m vectors.
     LanczosScalars lanczos_begin(const void* psi, void* V, int m);
+    // A whole build of m vectors in one launch (states of few rows), the product
+    // taken from a coefficient table of the handle's realisations.
+    bool one_launch_lanczos(int m, int n_masks) const;
+    LanczosScalars lanczos_build(const void* psi, void* V, int m, const void* table, const MaskRec* masks, int n_masks,
+                                 const int32_t* real_of_col);
     // Iteration j after the product w = H V_j: two passes of classical
     // Gram-Schmidt against V_0 .. V_j, alpha_j, beta_j, the invariant-subspace
     // test and V_{j+1} (zero for a column whose subspace became invariant).
@@ -71,6 +76,7 @@ private:
     };
     dim3 reduce_grid() const;
     bool small_lanczos(int m) const;
+    LanczosScalars lanczos_arrays(int m);
     Sums finished(const double* part, int G, int n, const char* slot);
     Sums dots(const void* V, int k0, int kk, const void* w, const std::string& slot);
     Sums subtract(void* w, const void* V, int k0, int kk, Sums p, const char* norm_slot);

@@ -1,5 +1,6 @@
 """The Lanczos iteration's launch paths against exact exponentials in plain
-torch: states of at most 2,048 rows (one launch per iteration) and just above,
+numpy: states of at most 256 rows (a whole build in one launch, up to 8,192
+basis entries), of at most 2,048 rows (one launch per iteration) and just above,
 bases below, at and above the 16 vectors one sweep serves, single columns and
 blocks, in both precisions; and a zero column, which stays zero."""
 import numpy as np
@@ -23,7 +24,7 @@ def _taylor(H, psi, z):
 
 
 @pytest.mark.parametrize("dtype", list(TOL))
-@pytest.mark.parametrize("N,nvec,m", [(8, 1, 12), (20, 1, 16), (22, 2, 17), (22, 1, 33), (24, 1, 15), (24, 3, 20)])
+@pytest.mark.parametrize("N,nvec,m", [(4, 1, 4), (6, 3, 8), (8, 1, 12), (16, 2, 32), (16, 1, 33), (18, 1, 20), (20, 1, 16), (22, 2, 17), (22, 1, 33), (24, 1, 15), (24, 3, 20)])
 def test_step_matches_exponential(N, nvec, m, dtype):
     J = inputs.couplings(N, 5)
     psi = np.stack([inputs.typical_state(N, 50 + c) for c in range(nvec)])
