@@ -40,25 +40,51 @@ inline dim3 grid_of(const Shape& S, bool reduction)
     return dim3(gx, S.B);
 }
 
-// Workgroup sums of a[0..n) (n <= N, the same n on every thread): each wave
-// adds its 64 lanes with a butterfly of lane exchanges, lane 0 of every wave
-// stores its sums in red[wave][i], and after one barrier thread i < n returns
-// red[0][i] + red[1][i] + red[2][i] + red[3][i] (others return 0).  red holds
-// kWaves * N doubles.
-template <int N>
-__device__ __forceinline__ double block_sum(double (&a)[N], int n, double* red)
+constexpr int ceil_pow2(int n) { return n <= 1 ? 1 : 2 * ceil_pow2((n + 1) / 2); }
+
+// One halving step of wave_scatter_sum: P values per lane become P / 2, each the
+// sum over this lane and the lane that differs in lane bit OFF; lanes with the
+// bit clear keep the lower half of the values, the others the upper half.
+template <int P, int OFF, int N>
+__device__ __forceinline__ void scatter_step(double (&v)[N], int lane)
 {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if constexpr (P > 1) {
+        const bool up = (lane & OFF) != 0;
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-        if (i >= n) break;
+        for (int i = 0; i < P / 2; ++i) {
+            const double keep = up ? v[i + P / 2] : v[i], give = up ? v[i] : v[i + P / 2];
+            v[i] = keep + __shfl_xor(give, OFF, 64);
+        }
+        scatter_step<P / 2, OFF / 2>(v, lane);
+    } else {
+        // one value left: the lane bits below pick copies of it
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) a[i] += __shfl_xor(a[i], off, 64);
-        if (lane == 0) red[wave * N + i] = a[i];
+        for (int off = OFF; off > 0; off >>= 1) v[0] += __shfl_xor(v[0], off, 64);
     }
+}
+
+// Workgroup sums of a[0..N): each wave adds its 64 lanes by halving exchanges
+// (P + 5 - log2 P lane exchanges for P = N rounded up to a power of two; a
+// butterfly per value takes 6 N and was a third of a sweep over 16 vectors of
+// 2^16 rows: 10 us, 7 with it), the lane that holds value i stores it in
+// red[wave][i], and after one barrier thread i < N returns red[0][i] + red[1][i]
+// + red[2][i] + red[3][i] (others return 0).  red holds kWaves * N doubles.
+template <int N>
+__device__ __forceinline__ double block_sum(double (&a)[N], double* red)
+{
+    constexpr int P = ceil_pow2(N);
+    static_assert(P <= 64, "block_sum: at most 64 values");
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    double v[P];
+#pragma unroll
+    for (int i = 0; i < P; ++i) v[i] = i < N ? a[i] : 0.0;
+    scatter_step<P, 32>(v, lane);
+    // lane bit 5 chose the top bit of the value's index, and so on down
+    const int i = lane / (64 / P);
+    if (lane % (64 / P) == 0 && i < N) red[wave * N + i] = v[0];
     __syncthreads();
     double s = 0.0;
-    if ((int)threadIdx.x < n)
+    if ((int)threadIdx.x < N)
         for (int w = 0; w < kWaves; ++w) s += red[w * N + threadIdx.x];
     return s;
 }
@@ -189,7 +215,7 @@ __global__ void __launch_bounds__(RB) k_multidot(const cplx<R>* __restrict__ V, 
             a[2 * k + 1] += vr * bi - vi * br;
         }
     }
-    const double t = block_sum(a, 2 * K, red);
+    const double t = block_sum(a, red);
     // thread i < 2K holds (k, re/im) = (i / 2, i % 2)
     if ((int)threadIdx.x < 2 * K)
         partial[((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * (2 * K) + threadIdx.x] = t;
@@ -235,7 +261,7 @@ __global__ void __launch_bounds__(RB) k_update(cplx<R>* __restrict__ w, const cp
     }
     if (!partial) return;
     double a[1] = {nrm};
-    const double t = block_sum(a, 1, tmp);
+    const double t = block_sum(a, tmp);
     if (threadIdx.x == 0) partial[(int64_t)c * gridDim.x + blockIdx.x] = t;
 }
 
@@ -285,7 +311,7 @@ __global__ void __launch_bounds__(RB) k_update_dot(cplx<R>* __restrict__ w, cons
             a[2 * k + 1] += vr * oi - vi * orr;
         }
     }
-    const double t = block_sum(a, 2 * K, red);
+    const double t = block_sum(a, red);
     if ((int)threadIdx.x < 2 * K) partial[((int64_t)c * gridDim.x + blockIdx.x) * (2 * K) + threadIdx.x] = t;
 }
 
@@ -404,7 +430,7 @@ __global__ void __launch_bounds__(RB) k_lanczos_next(const cplx<R>* __restrict__
     double a[2] = {0.0, 0.0};
     for (int g = threadIdx.x; g < G1; g += RB) a[0] += p1[((int64_t)c * G1 + g) * n + at];
     for (int g = threadIdx.x; g < G2; g += RB) a[1] += p2[((int64_t)c * G2 + g) * n + at];
-    const double t = block_sum(a, 2, red);
+    const double t = block_sum(a, red);
     __syncthreads();
     if (threadIdx.x < 2) tmp[threadIdx.x] = t;
     __syncthreads();
