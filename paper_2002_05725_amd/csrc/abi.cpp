@@ -615,10 +615,7 @@ syk_status syk_coupling_overlaps(syk_terms t, int npairs, const void* const* g, 
         double* bins = (double*)t->ws.get("overlap_bins", T.n_bins * 2 * sizeof(double));
         SYK_HIP(hipMemsetAsync(bins, 0, T.n_bins * 2 * sizeof(double), c.stream));
         grad_bins(*t, gv, vv, wv, bins, c.stream);
-        std::vector<double> hb(T.n_bins * 2);
-        SYK_HIP(hipMemcpyAsync(hb.data(), bins, hb.size() * sizeof(double), hipMemcpyDeviceToHost, c.stream));
-        SYK_HIP(hipStreamSynchronize(c.stream));
-        couplings_from_bins(T, hb.data(), out);
+        couplings_from_bins(*t, bins, out, c.stream);
     });
 }
 

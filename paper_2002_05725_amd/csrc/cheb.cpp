@@ -309,10 +309,7 @@ void cheb_otoc(BlockCtx& c, int i, int j, double beta, double t, const ChebSetti
         c.ops.combine(seed, u, 1, std::vector<C>{-2.0 * f / Z});
         chain_backward(st, ch.U, "ckU", seed, bins);
     }
-    std::vector<double> hb(T.n_bins * 2);
-    SYK_HIP(hipMemcpyAsync(hb.data(), bins, hb.size() * sizeof(double), hipMemcpyDeviceToHost, c.stream));
-    SYK_HIP(hipStreamSynchronize(c.stream));
-    couplings_from_bins(T, hb.data(), grad);
+    couplings_from_bins(c.h, bins, grad, c.stream);
 }
 
 }  // namespace syk

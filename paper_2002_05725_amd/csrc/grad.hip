@@ -151,11 +151,14 @@ __global__ void __launch_bounds__(256) k_cheb_rec(cplx<R>* out, const cplx<R>* _
     }
 }
 
+constexpr uint32_t kGradFill = 768;   // workgroups the chip holds (three per CU)
+
 struct GLayout {
     int tile_bits;                        // rows per tile = 2^tile_bits
     int lane_bits;                        // in-wave lane bits that index rows (6, fewer for tiny states)
     uint32_t n_tiles;
-    uint32_t tile_groups, chunk_groups;   // grid = tile_groups x chunk_groups workgroups
+    uint32_t tile_groups, chunk_groups;   // grid = (tile_groups x chunk_groups) x pair_groups workgroups
+    uint32_t pair_groups;                 // the pairs, split for small states; each group fills its own partial slices
     int n_chunks;
     int npairs;
     int M;
@@ -209,7 +212,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
     }
     // workgroup (t, s) of the grid: tiles t, t + tile_groups, ...; chunks s, s + chunk_groups, ...
     const uint32_t tg = blockIdx.x % L.tile_groups, sg = blockIdx.x / L.tile_groups;
-    double* mine = partial + (uint64_t)tg * L.n_bins * 2;
+    double* mine = partial + ((uint64_t)blockIdx.y * L.tile_groups + tg) * L.n_bins * 2;
+    // this workgroup's pairs
+    const int stages = L.npairs / PP;
+    const int p_begin = (int)((uint32_t)stages * blockIdx.y / L.pair_groups) * PP;
+    const int p_end = (int)((uint32_t)stages * (blockIdx.y + 1) / L.pair_groups) * PP;
 
     for (int ch = (int)sg; ch < L.n_chunks; ch += (int)L.chunk_groups) {
         const GChunk C = chunks[ch];
@@ -236,7 +243,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) k
                 for (int h = 0; h < 2; ++h) acc_re[j][h] = acc_im[j][h] = 0.0;
 
             // PP pairs at a time (the host pads the list with zero-weight pairs)
-            for (int p0 = 0; p0 < L.npairs; p0 += PP) {
+            for (int p0 = p_begin; p0 < p_end; p0 += PP) {
                 c128 gk[PP][RPT];   // w_p g_p on the lane's rows (every wave loads all rows)
 #pragma unroll
                 for (int u = 0; u < PP; ++u) {
@@ -544,11 +551,67 @@ __global__ void k_bins_reduce(const double* __restrict__ partial, int nblk, uint
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     double s = 0.0;
+#pragma unroll 8
     for (int b = 0; b < nblk; ++b) s += partial[(uint64_t)b * n + i];
     out[i] += s;
 }
 
+// out[n] = Re of the n-th coupling's derivative from the bins (terms.hpp), one
+// thread per coupling: each bin is used with the sign of the term's own table of a
+// unit coupling, sums in index order.  On the host this took 50 ns per coupling
+// (N=24 0.5 ms, N=36 2.8 ms, beside kernels of 0.16 and 14.8 ms).
+__global__ void __launch_bounds__(256) k_couplings(const TermRef* __restrict__ terms, const MaskRec* __restrict__ masks,
+                                                   const uint32_t* __restrict__ bin_off,
+                                                   const double* __restrict__ bins, uint32_t n, double* __restrict__ out)
+{
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i >= n) return;
+    const TermRef t = terms[i];
+    const MaskRec m = masks[t.mask];
+    const double* b = bins + 2 * (uint64_t)bin_off[t.mask];
+    const uint32_t type = m.type_tab >> 28;
+    // Re(i^ph x): the real or the imaginary component, signed
+    const uint32_t comp = (uint32_t)t.ph & 1u;
+    double s = 0.0;
+    if (type == MASK_QUAD) {
+        uint32_t zq = 0;   // the term's Z at the flipped qubits
+#pragma unroll
+        for (int j = 0; j < 4; ++j) zq |= bit(t.z, mask_q(m.qpack, j)) << j;
+#pragma unroll
+        for (uint32_t idx = 0; idx < 16; ++idx) s += flip(b[2 * idx + comp], parity(~idx & zq));   // s = the opposite bits
+    } else if (type == MASK_PAIR) {
+        const uint32_t zq = bit(t.z, mask_q(m.qpack, 0)) | (bit(t.z, mask_q(m.qpack, 1)) << 1);
+#pragma unroll
+        for (uint32_t idx = 0; idx < 4; ++idx)
+            s += flip(b[2 * idx + comp] - 2.0 * b[2 * (4 + 4 * (uint32_t)t.slot + idx) + comp], parity(~idx & zq & 3u));
+    } else {
+        s = b[2 * (uint32_t)t.slot + comp];
+    }
+    // i^0 = 1, i (a + i b): -b, i^2 = -1, i^3: b
+    out[i] = 0.25 * ((t.ph == 1 || t.ph == 2) ? -s : s);
+}
+
 }  // namespace
+
+void couplings_from_bins(syk_terms_s& h, const double* bins_dev, double* out, hipStream_t st)
+{
+    const TermTables& T = h.host;
+    const size_t n = T.terms.size();
+    if (!h.term_refs.p) {   // once per handle; finished before use on any stream
+        std::vector<uint32_t> off(T.bin_off.begin(), T.bin_off.end());
+        const size_t tb = n * sizeof(TermRef), ob = off.size() * sizeof(uint32_t);
+        h.term_refs.ensure(tb + ob);
+        SYK_HIP(hipMemcpy(h.term_refs.p, T.terms.data(), tb, hipMemcpyHostToDevice));
+        SYK_HIP(hipMemcpy(static_cast<char*>(h.term_refs.p) + tb, off.data(), ob, hipMemcpyHostToDevice));
+    }
+    const TermRef* tr = h.term_refs.as<TermRef>();
+    double* host = static_cast<double*>(h.pinned.get(n * sizeof(double)));
+    hipLaunchKernelGGL(k_couplings, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, tr, h.H.masks,
+                       reinterpret_cast<const uint32_t*>(tr + n), bins_dev, (uint32_t)n, host);
+    SYK_HIP(hipGetLastError());
+    SYK_HIP(hipStreamSynchronize(st));
+    std::memcpy(out, host, n * sizeof(double));
+}
 
 GradChunks make_grad_chunks(const std::vector<MaskRec>& masks, const std::vector<uint8_t>& layout_of,
                             const std::vector<uint64_t>& bin_off, uint64_t n_bins, int tile_bits, int lane_bits)
@@ -730,6 +793,17 @@ void grad_bins(syk_terms_s& h, const std::vector<const void*>& g, const std::vec
     L.tile_groups = (uint32_t)nblk;
     L.chunk_groups = (uint32_t)std::max(1, std::min(L.n_chunks, 12288 / nblk));
 
+    // Small states have few tiles and chunks: the pairs are split over workgroups
+    // too, up to the workgroups the chip holds (each walks its pairs in series, two
+    // per stage, and every stage waits for a round trip to memory).  Kernel time
+    // with 32 pairs, us, before -> split: N=20 229 -> 77, N=24 255 -> 164; from N=28
+    // on one group (twice or four times as many workgroups: N=24 +10% / +30%).
+    const int np = (npairs + kGradPairsPerStage - 1) / kGradPairsPerStage * kGradPairsPerStage;
+    const uint32_t wg = L.tile_groups * L.chunk_groups;
+    L.pair_groups = std::min<uint32_t>((uint32_t)(np / kGradPairsPerStage), std::max<uint32_t>(1u, kGradFill / wg));
+    L.pair_groups = std::max<uint32_t>(1u, std::min<uint32_t>(L.pair_groups, 512u / L.tile_groups));
+    const int slices = nblk * (int)L.pair_groups;
+
     // rotated copies of the pair vectors for the masks of the second layout
     const uint64_t dim = (uint64_t)1 << M;
     std::vector<const void*> gr(npairs), vr(npairs);
@@ -748,7 +822,6 @@ void grad_bins(syk_terms_s& h, const std::vector<const void*>& g, const std::vec
     // pointer lists and weights: one small synchronous upload.  The list is
     // padded to a multiple of kGradPairsPerStage with copies of pair 0 of
     // weight 0 (their products are exact zeros).
-    const int np = (npairs + kGradPairsPerStage - 1) / kGradPairsPerStage * kGradPairsPerStage;
     L.npairs = np;
     std::vector<uint64_t> host(5 * (size_t)np);
     for (int p = 0; p < np; ++p) {
@@ -769,13 +842,13 @@ void grad_bins(syk_terms_s& h, const std::vector<const void*>& g, const std::vec
     const c128* const* vlr = gl + 3 * np;
     const double* wl = (const double*)(gl + 4 * np);
 
-    double* partial = (double*)h.ws.get("grad_partial", (size_t)nblk * T.n_bins * 2 * sizeof(double));
+    double* partial = (double*)h.ws.get("grad_partial", (size_t)slices * T.n_bins * 2 * sizeof(double));
     const KRec* krec = it->second->as<KRec>();
     const GChunk* chunks = reinterpret_cast<const GChunk*>(krec + T.masks.size());
     const GRec* grec = reinterpret_cast<const GRec*>(chunks + L.n_chunks);
     const uint32_t* members = reinterpret_cast<const uint32_t*>(grec + h.grad_nmembers[key] + kGradRecPad);
     const uint32_t* local = members + h.grad_nmembers[key];
-    const dim3 grid(nblk * L.chunk_groups), block(256);
+    const dim3 grid(nblk * L.chunk_groups, L.pair_groups), block(256);
     switch (kb) {
     case 0: hipLaunchKernelGGL(k_grad_bins<0>, grid, block, 0, st, krec, chunks, members, local, grec, H.dz, L, gl, vl, glr, vlr, wl, partial); break;
     case 1: hipLaunchKernelGGL(k_grad_bins<1>, grid, block, 0, st, krec, chunks, members, local, grec, H.dz, L, gl, vl, glr, vlr, wl, partial); break;
@@ -785,7 +858,7 @@ void grad_bins(syk_terms_s& h, const std::vector<const void*>& g, const std::vec
     }
     SYK_HIP(hipGetLastError());
     const uint64_t n = 2 * T.n_bins;
-    hipLaunchKernelGGL(k_bins_reduce, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, partial, nblk, n, bins_dev);
+    hipLaunchKernelGGL(k_bins_reduce, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, partial, slices, n, bins_dev);
     SYK_HIP(hipGetLastError());
 }
 

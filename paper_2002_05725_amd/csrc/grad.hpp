@@ -68,4 +68,8 @@ void cheb_rec(syk_dtype dtype, int64_t n, void* out, const void* w, const void* 
 void grad_bins(syk_terms_s& h, const std::vector<const void*>& g, const std::vector<const void*>& v,
                const std::vector<double>& w, double* bins_dev, hipStream_t st);
 
+// d/dJ_n Re <g|H v> for every coupling n from the derivative bins (terms.hpp) on
+// the device, to the host array out; synchronises the stream.
+void couplings_from_bins(syk_terms_s& h, const double* bins_dev, double* out, hipStream_t st);
+
 }  // namespace syk

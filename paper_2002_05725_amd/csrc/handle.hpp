@@ -97,6 +97,7 @@ struct syk_terms_s {
     syk::PinnedBuf pinned;          // results of reductions, written by kernels
     std::map<int, std::unique_ptr<syk::DevBuf>> grad_chunks;   // per (tile_bits, layouts)
     std::map<int, int> grad_nchunks, grad_nmembers;
+    syk::DevBuf term_refs;          // TermRef of every coupling, then the masks' bin offsets (first use)
     // H restricted to each fermion-parity sector, built on first use
     struct Sector {
         syk::TermTables host;

@@ -177,43 +177,6 @@ void build_tables(int N, int n_real, const double* J, TermTables& T)
     }
 }
 
-void couplings_from_bins(const TermTables& T, const double* bins, double* out)
-{
-    typedef std::complex<double> C;
-    auto bin = [&](uint64_t i) { return C(bins[2 * i], bins[2 * i + 1]); };
-    const int M = T.M;
-    for (size_t n = 0; n < T.terms.size(); ++n) {
-        const TermRef& tr = T.terms[n];
-        const MaskRec& m = T.masks[tr.mask];
-        const uint64_t off = T.bin_off[tr.mask];
-        const uint32_t type = m.type_tab >> 28;
-        const C ph = iphase(tr.ph) * 0.25;
-        C s = 0.0;
-        if (type == MASK_QUAD) {
-            // the term's own 16-entry table with J = 1 (same construction as build_tables)
-            for (int idx = 0; idx < 16; ++idx) {
-                uint32_t s_loc = 0;
-                for (int j = 0; j < 4; ++j)
-                    if (!((idx >> j) & 1)) s_loc |= 1u << mask_q(m.qpack, j);
-                const double sg = (__builtin_popcount(s_loc & tr.z) & 1) ? -1.0 : 1.0;
-                s += sg * ph * bin(off + idx);
-            }
-        } else if (type == MASK_PAIR) {
-            const uint32_t qa = mask_q(m.qpack, 0), qb = mask_q(m.qpack, 1);
-            const int e0 = (int)((tr.z >> qa) & 1u), e1 = (int)((tr.z >> qb) & 1u);
-            for (int idx = 0; idx < 4; ++idx) {
-                const int sa = !(idx & 1), sb = !((idx >> 1) & 1);
-                const double sg = (((sa & e0) ^ (sb & e1)) & 1) ? -1.0 : 1.0;
-                s += sg * ph * (bin(off + idx) - 2.0 * bin(off + 4 + 4 * (uint64_t)tr.slot + idx));
-            }
-        } else {
-            s = ph * bin(off + tr.slot);
-        }
-        out[n] = s.real();
-        (void)M;
-    }
-}
-
 }  // namespace syk
 
 namespace syk {

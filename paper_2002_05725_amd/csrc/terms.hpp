@@ -90,8 +90,6 @@ struct TermTables {
 //   QUAD  B[idx]            = sum_r conj(g[r]) (-1)^{|r & zbase|} v[r ^ x] over rows with bits idx at q0..q3
 //   PAIR  B[idx], C_c[idx]  = the same over rows with bits idx at q0, q1 (C_c: only rows with r_c = 1)
 //   DIAG  E_n               = sum_r conj(g[r]) (-1)^{|r & dz_n|} v[r]
-// d/dJ_n Re <g|H v> for every coupling n, from the bins.
-void couplings_from_bins(const TermTables& T, const double* bins /* n_bins (re, im) */, double* out);
 
 void build_tables(int N, int n_real, const double* J, TermTables& out);
 

@@ -24,7 +24,7 @@ def _taylor(H, psi, z):
 
 
 @pytest.mark.parametrize("dtype", list(TOL))
-@pytest.mark.parametrize("N,nvec,m", [(4, 1, 4), (6, 3, 8), (8, 1, 12), (16, 2, 32), (16, 1, 33), (18, 1, 20), (20, 1, 16), (22, 2, 17), (22, 1, 33), (24, 1, 15), (24, 3, 20)])
+@pytest.mark.parametrize("N,nvec,m", [(4, 1, 4), (6, 3, 8), (8, 1, 12), (16, 2, 32), (16, 1, 33), (18, 1, 20), (20, 1, 16), (22, 2, 17), (22, 1, 33), (24, 1, 15), (24, 3, 20), (26, 1, 30), (24, 2, 35)])
 def test_step_matches_exponential(N, nvec, m, dtype):
     J = inputs.couplings(N, 5)
     psi = np.stack([inputs.typical_state(N, 50 + c) for c in range(nvec)])
