@@ -729,17 +729,17 @@ struct KColumns {
 // workgroups of 16 waves in flight with a few masks each; the groups' sums are
 // added in a fixed order.  Bound by its loads' latency (table entry, mask, then
 // the amplitude), up to 2^12 rows by the table's bytes from L2 and the
-// Infinity Cache (37 MB at N=24 in complex128).
-template <typename R>
-__global__ void __launch_bounds__(kTableThreads) k_apply_table(const cplx<R>* __restrict__ table,
-                                                               const MaskRec* __restrict__ masks, int n_masks,
-                                                               KColumns C, uint32_t dim,
-                                                               const cplx<R>* __restrict__ psi, cplx<R>* __restrict__ out)
+// Infinity Cache (37 MB at N=24 in complex128).  REC: the product goes straight
+// into a Chebyshev recurrence step (RecArgs) instead of out, one launch for two
+// (the reverse sweep at N=24 is mostly such pairs of short launches).
+template <typename R, bool REC>
+__device__ __forceinline__ void apply_table(const cplx<R>* __restrict__ table, const MaskRec* __restrict__ masks,
+                                            int n_masks, int rc, uint32_t dim, const cplx<R>* __restrict__ psi,
+                                            cplx<R>* out, const RecArgs& q)
 {
     __shared__ c128 red[kTableThreads / 64][kTableRows];
     const uint32_t tid = threadIdx.x, rl = tid % kTableRows, slot = tid / kTableRows;
     const uint32_t r = blockIdx.x * kTableRows + rl;
-    const int rc = C.real[blockIdx.y];
     const cplx<R>* t = table + ((uint64_t)rc * gridDim.x + blockIdx.x) * n_masks * kTableRows + tid;
     psi += (uint64_t)blockIdx.y * dim;
     double ar = 0.0, ai = 0.0;
@@ -774,8 +774,46 @@ __global__ void __launch_bounds__(kTableThreads) k_apply_table(const cplx<R>* __
         cplx<R> o;
         o.re = (R)sr;
         o.im = (R)si;
+        if constexpr (REC) {   // one complex128 column; the formula of k_cheb_rec
+            const cplx<R> yv = psi[r];
+            double re = q.b * ((double)o.re - q.gamma * (double)yv.re);
+            double im = q.b * ((double)o.im - q.gamma * (double)yv.im);
+            if (q.z) {
+                const c128 zv = q.z[r];
+                re += q.s * zv.re;
+                im += q.s * zv.im;
+            }
+            if (q.x) {
+                const c128 xv = q.x[r];
+                re += q.c_re * xv.re - q.c_im * xv.im;
+                im += q.c_re * xv.im + q.c_im * xv.re;
+            }
+            o.re = (R)re;
+            o.im = (R)im;
+            if (q.acc) {
+                const c128 a = q.acc[r];
+                q.acc[r] = c128{a.re + q.ca_re * re - q.ca_im * im, a.im + q.ca_re * im + q.ca_im * re};
+            }
+        }
         out[(uint64_t)blockIdx.y * dim + r] = o;
     }
+}
+
+template <typename R>
+__global__ void __launch_bounds__(kTableThreads) k_apply_table(const cplx<R>* __restrict__ table,
+                                                               const MaskRec* __restrict__ masks, int n_masks,
+                                                               KColumns C, uint32_t dim,
+                                                               const cplx<R>* __restrict__ psi, cplx<R>* out)
+{
+    apply_table<R, false>(table, masks, n_masks, C.real[blockIdx.y], dim, psi, out, RecArgs{});
+}
+
+__global__ void __launch_bounds__(kTableThreads) k_apply_table_rec(const c128* __restrict__ table,
+                                                                   const MaskRec* __restrict__ masks, int n_masks,
+                                                                   uint32_t dim, const c128* __restrict__ psi, c128* out,
+                                                                   RecArgs q)
+{
+    apply_table<double, true>(table, masks, n_masks, 0, dim, psi, out, q);
 }
 
 uint32_t table_blocks(const HamiltonianDev& H)
@@ -1537,6 +1575,17 @@ const void* coefficient_table(const HamiltonianDev& H, const ApplyPlan& P, syk_d
     if (dtype == SYK_C128) ensure_table<double>(H, H.table_d, s);
     else ensure_table<float>(H, H.table_f, s);
     return (dtype == SYK_C128 ? H.table_d : H.table_f).p;
+}
+
+bool launch_apply_rec(const HamiltonianDev& H, const ApplyPlan& P, const void* psi, void* out, const RecArgs& q, hipStream_t s)
+{
+    const void* table = coefficient_table(H, P, SYK_C128, 1, s);
+    if (!table) return false;
+    hipLaunchKernelGGL(k_apply_table_rec, dim3(table_blocks(H), 1), dim3(kTableThreads), 0, s,
+                       static_cast<const c128*>(table), H.masks, (int)H.host_masks->size(), 1u << H.M,
+                       static_cast<const c128*>(psi), static_cast<c128*>(out), q);
+    SYK_HIP(hipGetLastError());
+    return true;
 }
 
 void launch_apply_h(const HamiltonianDev& H, syk_dtype dtype, int nvec, const int32_t* real_of_col,

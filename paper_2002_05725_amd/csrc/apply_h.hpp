@@ -114,6 +114,19 @@ void launch_transpose(syk_dtype dtype, const void* src, void* dst, int log_h, in
 // (small states; built on first use), or NULL: [realisation][block of 16 rows][mask][16].
 const void* coefficient_table(const HamiltonianDev& H, const ApplyPlan& P, syk_dtype dtype, int nvec, hipStream_t s);
 
+// One Chebyshev recurrence step on one complex128 column of realisation 0 with the
+// product formed in the same launch, for states whose products run from the
+// coefficient table (false: nothing was launched): out = b (H psi - gamma psi) +
+// s z + c x, acc += ca out.  Null pointers drop their term; out may alias z or x,
+// not psi.
+struct RecArgs {
+    const c128 *z, *x;
+    c128* acc;
+    double b, gamma, s, c_re, c_im, ca_re, ca_im;
+};
+bool launch_apply_rec(const HamiltonianDev& H, const ApplyPlan& P, const void* psi, void* out, const RecArgs& q,
+                      hipStream_t s);
+
 // out = H psi for nvec columns stored one after another; real_of_col: host array or NULL.
 void launch_apply_h(const HamiltonianDev& H, syk_dtype dtype, int nvec, const int32_t* real_of_col,
                     const void* psi, void* out, const ApplyPlan& P, hipStream_t s);

@@ -16,6 +16,7 @@
 // w_n = 2, Q = dH/dJ.  States of a chain are stored every checkpoint_every
 // operations and recomputed segment by segment.
 #include "cheb.hpp"
+#include "timing.hpp"
 
 #include <cmath>
 #include <cstdio>
@@ -59,12 +60,22 @@ struct Stepper {
         cheb_rec(c.dtype, n, out, w, y, z, x, acc, b, s.e_c, sz, cx, ca, c.stream);
     }
 
+    // The product of `in` and a recurrence step on it (y = in), in one launch where the library has one.
+    void product_rec(void* out, const void* in, const void* z, const void* x, void* acc, double b, double sz, C cx, C ca)
+    {
+        const RecArgs q{(const c128*)z, (const c128*)x, (c128*)acc, b, s.e_c, sz, cx.real(), cx.imag(), ca.real(), ca.imag()};
+        // (with kernel timing on, every product is a launch of its own)
+        if (!timing_enabled() && launch_apply_rec(*c.Hact, c.plan, in, out, q, c.stream)) return;
+        void* w = pool.get("w");
+        c.apply_H(in, w);
+        rec(out, w, in, z, x, acc, b, sz, cx, ca);
+    }
+
     // out = sum_n coef_n v_n with v_n = T_n(H~) in.  With `store`, v_n is left
     // in store[n] (out may then be null); else three rotating buffers are used.
     void forward(const ChebOp& op, const void* in, void* out, const std::vector<void*>* store)
     {
         const int K = (int)op.c.size() - 1;
-        void* w = pool.get("w");
         void* b[3] = {nullptr, nullptr, nullptr};
         auto vec = [&](int k) -> void* {
             if (store) return (*store)[k];
@@ -77,15 +88,13 @@ struct Stepper {
             v0 = (*store)[0];
         }
         if (out) c.ops.combine(out, v0, 1, std::vector<C>{op.c[0]});
-        c.apply_H(v0, w);
         void* v1 = vec(1);
-        rec(v1, w, v0, nullptr, nullptr, out, 1.0 / s.e_h, 0.0, 0.0, op.c[1]);
+        product_rec(v1, v0, nullptr, nullptr, out, 1.0 / s.e_h, 0.0, 0.0, op.c[1]);
         const void* pm = v0;   // v_{n-2}
         const void* pc = v1;   // v_{n-1}
         for (int k = 2; k <= K; ++k) {
-            c.apply_H(pc, w);
             void* nv = vec(k);
-            rec(nv, w, pc, pm, nullptr, out, 2.0 / s.e_h, -1.0, 0.0, op.c[k]);
+            product_rec(nv, pc, pm, nullptr, out, 2.0 / s.e_h, -1.0, 0.0, op.c[k]);
             pm = pc;
             pc = nv;
         }
@@ -106,13 +115,11 @@ struct Stepper {
             for (int k = 0; k <= K; ++k) V[k] = pool.get("V", k);
             forward(op, in, nullptr, &V);
         }
-        void* w = pool.get("w");
         c.ops.combine(G[K], lam, 1, std::vector<C>{std::conj(op.c[K])});
         for (int k = K - 1; k >= 0; --k) {
-            c.apply_H(G[k + 1], w);
             void* out = (k == 0) ? lam_out : G[k];
             const void* z = (k + 2 <= K) ? G[k + 2] : nullptr;
-            rec(out, w, G[k + 1], z, lam, nullptr, (k == 0 ? 1.0 : 2.0) / s.e_h, -1.0, std::conj(op.c[k]), 0.0);
+            product_rec(out, G[k + 1], z, lam, nullptr, (k == 0 ? 1.0 : 2.0) / s.e_h, -1.0, std::conj(op.c[k]), 0.0);
         }
         // the bins add linearly over pairs: at most kGradMaxPairs pairs per call
         for (int k0 = 0; k0 < K; k0 += kGradMaxPairs) {
