@@ -55,8 +55,11 @@ def log(msg):
 
 
 def kernel_source_hash() -> str:
-    with open(os.path.join(ROOT, "paper_2002_05725_amd", "csrc", "apply_h.hip"), "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for name in ("apply_h.hip", "apply_groups.hpp"):
+        with open(os.path.join(ROOT, "paper_2002_05725_amd", "csrc", name), "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def traffic_from_profile(workload_key: str):
