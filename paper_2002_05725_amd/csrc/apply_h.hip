@@ -839,9 +839,9 @@ bool use_table(const HamiltonianDev& H, const ApplyPlan& P, int nvec, size_t esz
 
 // Builds the table of an element type the first time it is needed.
 template <typename R>
-void ensure_table(const HamiltonianDev& H, DevBuf& buf, hipStream_t s)
+void ensure_table(const HamiltonianDev& H, TableBuf& buf, hipStream_t s)
 {
-    if (buf.p) return;
+    if (buf.ready) return;
     const size_t n = table_entries(H);
     buf.ensure(n * H.n_real * sizeof(cplx<R>));
     KTerms<double> T{H.tab4_d, H.qinfo, H.phi2_d, H.w2_d, nullptr, H.n_real, H.M};
@@ -849,6 +849,7 @@ void ensure_table(const HamiltonianDev& H, DevBuf& buf, hipStream_t s)
                        (int)H.host_masks->size(), H.dz, H.dw_d, H.n_diag, 1u << H.M, table_blocks(H), buf.as<cplx<R>>());
     SYK_HIP(hipGetLastError());
     SYK_HIP(hipStreamSynchronize(s));   // once per handle: later calls may come on other streams
+    buf.ready = true;
 }
 
 template <typename R>
@@ -1341,8 +1342,8 @@ const HamiltonianDev::GroupTables& group_tables_for(const HamiltonianDev& H, con
         const dim3 og((n16 + 255) / 256, (uint32_t)H.n_real), pg((uint32_t)H.host_masks->size(), (uint32_t)H.n_real);
         size_t n_pairs = 0;
         for (const MaskRec& m : *H.host_masks) n_pairs += (m.type_tab >> 28) == MASK_PAIR;
-        DevBuf& pt = esz == 16 ? H.pair_tab_d : H.pair_tab_f;
-        const bool need = pt.p == nullptr;
+        TableBuf& pt = esz == 16 ? H.pair_tab_d : H.pair_tab_f;
+        const bool need = !pt.ready;
         if (need) pt.ensure(std::max<size_t>(n_pairs * H.n_real * pair_table_size(H.M) * esz, 64));
         auto build = [&](auto zero, const auto* tab4) {
             typedef decltype(zero) R;
@@ -1357,6 +1358,7 @@ const HamiltonianDev::GroupTables& group_tables_for(const HamiltonianDev& H, con
         else build(0.0f, H.tab4_f);
         SYK_HIP(hipGetLastError());
         SYK_HIP(hipStreamSynchronize(0));
+        pt.ready = true;
         up(t->far, G.far);
         if (P.parts > 1) up(t->part_chunk, part_bounds(G.cost, P.parts));
         it = H.group_tables.emplace(key, std::move(t)).first;
@@ -1544,7 +1546,7 @@ void launch_apply_h_noalloc(const HamiltonianDev& H, int device, syk_dtype dtype
     const size_t esz = elem_bytes(dtype);
     const uint64_t dim = (uint64_t)1 << H.M;
     if (use_table(H, P, nvec, esz)) {
-        if (!(dtype == SYK_C128 ? H.table_d : H.table_f).p)
+        if (!(dtype == SYK_C128 ? H.table_d : H.table_f).ready)
             throw Error(SYK_EINVAL, "apply_H_noalloc: the handle has no tables for this dtype and block width yet "
                                     "(call syk_apply_H once with them first)");
         launch_table_any(H, dtype, nvec, real_of_col, psi, out, s);

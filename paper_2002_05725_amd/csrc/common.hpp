@@ -77,6 +77,12 @@ struct DevBuf {
     T* as() const { return static_cast<T*>(p); }
 };
 
+// A device table built on first use.  `ready` is set once the work that fills it
+// has finished: after a launch or a wait that failed, the next use fills it again.
+struct TableBuf : DevBuf {
+    bool ready = false;
+};
+
 // Pinned host buffer owned by the library, read by the host after the stream
 // that wrote it is synchronised.
 struct PinnedBuf {

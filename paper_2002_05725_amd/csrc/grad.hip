@@ -597,12 +597,13 @@ void couplings_from_bins(syk_terms_s& h, const double* bins_dev, double* out, hi
 {
     const TermTables& T = h.host;
     const size_t n = T.terms.size();
-    if (!h.term_refs.p) {   // once per handle; finished before use on any stream
+    if (!h.term_refs.ready) {   // once per handle; finished before use on any stream
         std::vector<uint32_t> off(T.bin_off.begin(), T.bin_off.end());
         const size_t tb = n * sizeof(TermRef), ob = off.size() * sizeof(uint32_t);
         h.term_refs.ensure(tb + ob);
         SYK_HIP(hipMemcpy(h.term_refs.p, T.terms.data(), tb, hipMemcpyHostToDevice));
         SYK_HIP(hipMemcpy(static_cast<char*>(h.term_refs.p) + tb, off.data(), ob, hipMemcpyHostToDevice));
+        h.term_refs.ready = true;
     }
     const TermRef* tr = h.term_refs.as<TermRef>();
     double* host = static_cast<double*>(h.pinned.get(n * sizeof(double)));

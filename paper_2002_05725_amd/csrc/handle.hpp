@@ -38,12 +38,12 @@ struct HamiltonianDev {
         DevBuf chunks, groups, tables, pairs, far, part_chunk;
         int n_chunks = 0, n_far = 0, n_tables = 0;
     };
-    mutable DevBuf pair_tab_d, pair_tab_f;   // its PAIR tables per element type
+    mutable TableBuf pair_tab_d, pair_tab_f;   // its PAIR tables per element type
     mutable std::map<int, std::unique_ptr<GroupTables>> group_tables;
     // Rotated copies of psi and of the second layout's output (two-layout plans).
     mutable DevBuf rot_in, rot_out;
     // Coefficients of every mask and row of small states, per element type (filled on first use).
-    mutable DevBuf table_d, table_f;
+    mutable TableBuf table_d, table_f;
     // Partial sums of launches with their masks split over several workgroups per tile.
     mutable DevBuf parts;
     // The diagonal of H per realisation (FP64, [n_real][2^M]), filled on the
@@ -97,7 +97,7 @@ struct syk_terms_s {
     syk::PinnedBuf pinned;          // results of reductions, written by kernels
     std::map<int, std::unique_ptr<syk::DevBuf>> grad_chunks;   // per (tile_bits, layouts)
     std::map<int, int> grad_nchunks, grad_nmembers;
-    syk::DevBuf term_refs;          // TermRef of every coupling, then the masks' bin offsets (first use)
+    syk::TableBuf term_refs;        // TermRef of every coupling, then the masks' bin offsets (first use)
     // H restricted to each fermion-parity sector, built on first use
     struct Sector {
         syk::TermTables host;
