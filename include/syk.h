@@ -92,17 +92,21 @@ syk_status syk_apply_H(syk_terms t, syk_dtype dtype, int nvec, const int32_t* re
 
 /*
  * syk_apply_H for callers that cannot allocate device memory (code under HIP
- * graph capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * kernels and results as syk_apply_H (full space), with no hipMalloc, hipFree
- * or other allocation.  The buffers of the second, bit-rotated row layout
+ * graph capture, tight serving loops, harnesses that forbid hipMalloc): the
+ * product of syk_apply_H (full space), by the same kernels and to the same bits
+ * after a syk_apply_H of the same arguments, with no hipMalloc, hipFree or other
+ * allocation.  The buffers of the second, bit-rotated row layout
  * (psi copied in that layout and its partial output: 2 * min(nvec, 64) * dim
  * elements) and the partial sums of small states (at most 64 MiB, for products
  * of fewer than 2^21 rows over all columns) come from a device scratch array of
  * 128 MiB built into the library, which each device the library runs on holds
  * until the process ends (e.g. N <= 44 in complex128 or N <= 46 in complex64
- * for one column).  Larger requests return SYK_EINVAL.  The handle's per-dtype tables and
- * the diagonal of H are built by its first syk_apply_H call of that dtype and
- * block width: without one, SYK_EINVAL.  Every call on a device shares that
+ * for one column).  Larger requests return SYK_EINVAL.  The handle's tables and
+ * the diagonal of H are built by its syk_apply_H calls of that dtype, best with
+ * the same block width and real_of_col: the split of a small state's work goes
+ * with them, and tables built for another split serve at less than full speed,
+ * with sums in another order.  SYK_EINVAL if no call built any (or, with a tile
+ * given by syk_set_apply_tuning, none for that tile).  Every call on a device shares that
  * device's scratch, so calls that overlap in time on one device (other streams
  * or other threads) race and give wrong results; nothing in the scratch has to
  * start at zero.  The handle's device must be the current device.

@@ -1309,7 +1309,7 @@ std::vector<MaskRec> group_layout_masks(const std::vector<MaskRec>& masks, int M
 
 int group_tables_key(const ApplyPlan& P, uint32_t esz, int layout)
 {
-    return (((int)esz * 2 + P.two_layouts) * 2 + layout) * 256 + P.parts;
+    return (((int)esz * 2 + P.two_layouts) * 2 + layout) * 256 + P.cut;
 }
 
 const HamiltonianDev::GroupTables& group_tables_for(const HamiltonianDev& H, const ApplyPlan& P, uint32_t esz, int layout)
@@ -1320,7 +1320,7 @@ const HamiltonianDev::GroupTables& group_tables_for(const HamiltonianDev& H, con
         const std::vector<MaskRec> masks = group_layout_masks(*H.host_masks, H.M, P.two_layouts != 0, layout);
         // parts of a split launch: chunks of at most half a part's share, so that the parts come out even
         const double cost = (double)masks.size() + 4.0 * H.M * H.M / 2;
-        const GroupTables G = build_group_tables(masks, esz, P.parts > 1 ? std::max(6.0, 0.5 * cost / P.parts) : 0.0);
+        const GroupTables G = build_group_tables(masks, esz, P.cut > 1 ? std::max(6.0, 0.5 * cost / P.cut) : 0.0);
         std::unique_ptr<HamiltonianDev::GroupTables> t(new HamiltonianDev::GroupTables());
         t->n_chunks = (int)G.chunks.size();
         t->n_far = (int)G.far.size();
@@ -1360,7 +1360,7 @@ const HamiltonianDev::GroupTables& group_tables_for(const HamiltonianDev& H, con
         SYK_HIP(hipStreamSynchronize(0));
         pt.ready = true;
         up(t->far, G.far);
-        if (P.parts > 1) up(t->part_chunk, part_bounds(G.cost, P.parts));
+        if (P.cut > 1) up(t->part_chunk, part_bounds(G.cost, P.cut));
         it = H.group_tables.emplace(key, std::move(t)).first;
     }
     return *it->second;
@@ -1368,7 +1368,7 @@ const HamiltonianDev::GroupTables& group_tables_for(const HamiltonianDev& H, con
 
 int apply_tables_key(const ApplyPlan& P, uint32_t esz, int layout)
 {
-    return ((((P.tile_bits * 16 + P.lb) * 32 + (int)esz) * 2 + P.two_layouts) * 2 + layout) * 256 + P.parts;
+    return ((((P.tile_bits * 16 + P.lb) * 32 + (int)esz) * 2 + P.two_layouts) * 2 + layout) * 256 + P.cut;
 }
 
 const HamiltonianDev::ApplyTables& apply_tables_for(const HamiltonianDev& H, const ApplyPlan& P, uint32_t esz,
@@ -1384,7 +1384,7 @@ const HamiltonianDev::ApplyTables& apply_tables_for(const HamiltonianDev& H, con
         // parts of a split launch: chunks of at most half a part's share, so that the parts come out even
         const double cost = (double)masks.size() + 4.0 * H.M * H.M / 2;
         build_apply_tables(masks, P.tile_bits, P.lb, esz, ch, rc, far,
-                           P.parts > 1 ? std::max(6.0, 0.5 * cost / P.parts) : 0.0);
+                           P.cut > 1 ? std::max(6.0, 0.5 * cost / P.cut) : 0.0);
         std::unique_ptr<HamiltonianDev::ApplyTables> t(new HamiltonianDev::ApplyTables());
         t->n_chunks = (int)ch.size();
         t->n_far = (int)far.size();
@@ -1396,8 +1396,8 @@ const HamiltonianDev::ApplyTables& apply_tables_for(const HamiltonianDev& H, con
             t->far.ensure(far.size() * sizeof(FarRec));
             SYK_HIP(hipMemcpy(t->far.p, far.data(), far.size() * sizeof(FarRec), hipMemcpyHostToDevice));
         }
-        if (P.parts > 1) {
-            const std::vector<uint32_t> pb = part_bounds(chunk_costs(ch), P.parts);
+        if (P.cut > 1) {
+            const std::vector<uint32_t> pb = part_bounds(chunk_costs(ch), P.cut);
             t->part_chunk.ensure(pb.size() * sizeof(uint32_t));
             SYK_HIP(hipMemcpy(t->part_chunk.p, pb.data(), pb.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
         }
@@ -1485,6 +1485,7 @@ ApplyPlan plan_apply(int M, int nvec, syk_dtype dtype, const ApplyTuning* tune, 
     // with two layouts, 7.45 with one).
     P.two_layouts = (M - tb >= (P.parts > 1 ? 8 : P.groups ? 6 : 7) && tb >= 8) ? 1 : 0;
     P.rot = P.groups ? M - tb : tb;
+    P.cut = P.parts;
     return P;
 }
 
@@ -1509,7 +1510,9 @@ static ApplyPlan plan_of_call(const HamiltonianDev& H, const ApplyPlan& P, syk_d
     return Q.parts == 1 && Q.nc == 2 ? Q : P;
 }
 
-// Bytes of the partial sums of a split launch (FP64 for both state types).
+// Bytes of the partial sums of a split launch (FP64 for both state types): at
+// most kMaxPartsBytes, 2 * kSplitGroups workgroups' 2^11 rows or half as many of 2^12.
+constexpr size_t kMaxPartsBytes = (size_t)64 << 20;
 static size_t parts_bytes(const ApplyPlan& P, int nvec, uint64_t dim)
 {
     return P.parts > 1 ? (size_t)P.parts * std::min(nvec, kColsPerLaunch) * dim * sizeof(c128) : 0;
@@ -1538,36 +1541,125 @@ void* noalloc_scratch_ptr(int device)
     return p;
 }
 
+namespace {
+
+// Scratch of a launch: the rotated layout's two buffers, then the partial sums.
+size_t rot_bytes(const ApplyPlan& P, int nvec, uint64_t dim, size_t esz)
+{
+    return P.two_layouts ? 2 * (size_t)std::min(nvec, kColsPerLaunch) * dim * esz : 0;
+}
+
+// Whether the stream is recording into a graph.
+bool capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &c) != hipSuccess) {
+        (void)hipGetLastError();   // asked of the null stream while another one records
+        return false;
+    }
+    return c != hipStreamCaptureStatusNone;
+}
+
+// Whether the handle holds every table a launch of this plan reads.
+bool has_tables(const HamiltonianDev& H, const ApplyPlan& P, uint32_t esz)
+{
+    auto have = [&](int layout) {
+        return P.groups ? H.group_tables.count(group_tables_key(P, esz, layout)) != 0
+                        : H.apply_tables.count(apply_tables_key(P, esz, layout)) != 0;
+    };
+    return H.diag_ready && have(0) && (!P.two_layouts || have(1));
+}
+
+// How a product runs that may build and allocate nothing.
+struct Route {
+    bool table = false;   // from the coefficient table, else by the plan
+    ApplyPlan plan{};
+};
+
+// The call's own route if its tables exist and `fits` grants its scratch.  If they
+// do not (the split of the masks, and with it the tables, goes with the number of
+// columns and for complex64 with how they pair up), the same product from tables
+// that another call on the handle built: the coefficient table, or any plan's,
+// the split nearest to the call's own first; tables cut for a split whose partial
+// sums do not fit run unsplit, which needs none.  A tile given by the caller runs
+// as it is given or not at all.
+template <typename Fits>
+bool existing_route(const HamiltonianDev& H, const ApplyPlan& P, syk_dtype dtype, int nvec, const Fits& fits, Route& r)
+{
+    const uint32_t esz = (uint32_t)elem_bytes(dtype);
+    const bool table = (dtype == SYK_C128 ? H.table_d : H.table_f).ready;
+    r.plan = P;
+    r.table = table && use_table(H, P, nvec, esz);
+    if (r.table || (!use_table(H, P, nvec, esz) && has_tables(H, P, esz) && fits(P))) return true;
+    if (P.fixed_tile) return false;
+    r.table = table && H.M <= kTableMaxBits;
+    if (r.table) return true;
+    int best = -1;
+    auto consider = [&](ApplyPlan Q) {
+        if (!has_tables(H, Q, esz)) return;
+        Q.parts = Q.cut;
+        if (Q.parts > 1 && !fits(Q)) Q.parts = 1;
+        if (!fits(Q)) return;
+        const int away = std::abs(Q.cut - P.parts) + (Q.groups == P.groups ? 0 : 256);
+        if (best >= 0 && away >= best) return;
+        best = away;
+        r.plan = Q;
+    };
+    // the keys of group_tables_key and apply_tables_key, layout 0
+    for (const auto& kv : H.group_tables) {
+        ApplyPlan Q = P;
+        Q.cut = kv.first & 255;
+        Q.two_layouts = (kv.first >> 9) & 1;
+        Q.groups = 1;
+        Q.tile_bits = kGroupTileBits;
+        Q.rot = H.M - kGroupTileBits;
+        Q.lb = kLaneBits;
+        Q.nt = 1 << Q.lb;
+        Q.rpt = kGroupRows;
+        Q.nc = 1;
+        if (((kv.first >> 8) & 1) == 0 && (uint32_t)(kv.first >> 10) == esz) consider(Q);
+    }
+    for (const auto& kv : H.apply_tables) {
+        ApplyPlan Q = P;
+        Q.cut = kv.first & 255;
+        Q.two_layouts = (kv.first >> 9) & 1;
+        Q.groups = 0;
+        Q.tile_bits = kv.first >> 19;
+        Q.rot = Q.tile_bits;
+        Q.lb = (kv.first >> 15) & 15;
+        Q.nt = 1 << Q.lb;
+        Q.rpt = 1 << (Q.tile_bits - Q.lb);
+        Q.nc = 1;
+        if (((kv.first >> 8) & 1) == 0 && (uint32_t)((kv.first >> 10) & 31) == esz) consider(Q);
+    }
+    return best >= 0;
+}
+
+}  // namespace
+
 void launch_apply_h_noalloc(const HamiltonianDev& H, int device, syk_dtype dtype, int nvec,
                             const int32_t* real_of_col, const void* psi, void* out, const ApplyPlan& plan,
                             hipStream_t s)
 {
-    const ApplyPlan P = plan_of_call(H, plan, dtype, nvec, real_of_col);
+    const ApplyPlan own = plan_of_call(H, plan, dtype, nvec, real_of_col);
     const size_t esz = elem_bytes(dtype);
     const uint64_t dim = (uint64_t)1 << H.M;
-    if (use_table(H, P, nvec, esz)) {
-        if (!(dtype == SYK_C128 ? H.table_d : H.table_f).ready)
-            throw Error(SYK_EINVAL, "apply_H_noalloc: the handle has no tables for this dtype and block width yet "
-                                    "(call syk_apply_H once with them first)");
+    auto need = [&](const ApplyPlan& P) { return rot_bytes(P, nvec, dim, esz) + parts_bytes(P, nvec, dim); };
+    if (!use_table(H, own, nvec, esz) && need(own) > kNoAllocScratchBytes)
+        throw Error(SYK_EINVAL, "apply_H_noalloc: the call needs " + std::to_string(need(own)) +
+                                    " bytes of scratch, above the maximum of " +
+                                    std::to_string(kNoAllocScratchBytes));
+    Route r;
+    if (!existing_route(H, own, dtype, nvec, [&](const ApplyPlan& P) { return need(P) <= kNoAllocScratchBytes; }, r))
+        throw Error(SYK_EINVAL, "apply_H_noalloc: the handle has no tables for this dtype and block width yet "
+                                "(call syk_apply_H once with them first)");
+    if (r.table) {
         launch_table_any(H, dtype, nvec, real_of_col, psi, out, s);
         return;
     }
-    const size_t half = (size_t)std::min(nvec, kColsPerLaunch) * dim * esz;
-    const size_t rot = P.two_layouts ? 2 * half : 0, part = parts_bytes(P, nvec, dim);
-    if (rot + part > kNoAllocScratchBytes)
-        throw Error(SYK_EINVAL, "apply_H_noalloc: the call needs " + std::to_string(rot + part) +
-                                    " bytes of scratch, above the maximum of " +
-                                    std::to_string(kNoAllocScratchBytes));
-    // everything the handle builds on first use must exist already
-    auto have = [&](int layout) {
-        return P.groups ? H.group_tables.count(group_tables_key(P, (uint32_t)esz, layout)) != 0
-                        : H.apply_tables.count(apply_tables_key(P, (uint32_t)esz, layout)) != 0;
-    };
-    if (!H.diag_ready || !have(0) || (P.two_layouts && !have(1)))
-        throw Error(SYK_EINVAL, "apply_H_noalloc: the handle has no tables for this dtype and block width yet "
-                                "(call syk_apply_H once with them first)");
+    const size_t rot = rot_bytes(r.plan, nvec, dim, esz), part = parts_bytes(r.plan, nvec, dim);
     char* sp = rot + part > 0 ? static_cast<char*>(noalloc_scratch_ptr(device)) : nullptr;
-    launch_apply_impl(H, dtype, nvec, real_of_col, psi, out, P, s, rot ? sp : nullptr, rot ? sp + half : nullptr,
+    launch_apply_impl(H, dtype, nvec, real_of_col, psi, out, r.plan, s, rot ? sp : nullptr, rot ? sp + rot / 2 : nullptr,
                       part ? sp + rot : nullptr, false);
 }
 
@@ -1593,23 +1685,40 @@ bool launch_apply_rec(const HamiltonianDev& H, const ApplyPlan& P, const void* p
 void launch_apply_h(const HamiltonianDev& H, syk_dtype dtype, int nvec, const int32_t* real_of_col,
                     const void* psi, void* out, const ApplyPlan& plan, hipStream_t s)
 {
-    const ApplyPlan P = plan_of_call(H, plan, dtype, nvec, real_of_col);
-    if (coefficient_table(H, P, dtype, nvec, s)) {
+    ApplyPlan P = plan_of_call(H, plan, dtype, nvec, real_of_col);
+    const uint32_t esz = (uint32_t)elem_bytes(dtype);
+    const uint64_t dim = (uint64_t)1 << H.M;
+    bool table = use_table(H, P, nvec, esz);
+    auto held = [&](const ApplyPlan& Q) {
+        return rot_bytes(Q, nvec, dim, esz) / 2 <= std::min(H.rot_in.bytes, H.rot_out.bytes) &&
+               parts_bytes(Q, nvec, dim) <= H.parts.bytes();
+    };
+    if (table ? !(dtype == SYK_C128 ? H.table_d : H.table_f).ready : !has_tables(H, P, esz) || !held(P)) {
+        // A first call of its kind builds and allocates, unless its stream is under
+        // graph capture, where that is refused: then what the handle holds serves it.
+        Route r;
+        if (capturing(s) && existing_route(H, P, dtype, nvec, held, r)) {
+            table = r.table;
+            P = r.plan;
+        }
+    }
+    if (table) {
+        if (dtype == SYK_C128) ensure_table<double>(H, H.table_d, s);
+        else ensure_table<float>(H, H.table_f, s);
         timing_begin(s);
         launch_table_any(H, dtype, nvec, real_of_col, psi, out, s);
         timing_end(s);
         return;
     }
-    const bool two = P.two_layouts != 0;
-    if (two) {
-        const size_t bytes = (size_t)std::min(nvec, kColsPerLaunch) * ((uint64_t)1 << H.M) * elem_bytes(dtype);
-        H.rot_in.ensure(bytes);
-        H.rot_out.ensure(bytes);
+    const size_t rot = rot_bytes(P, nvec, dim, esz) / 2, part = parts_bytes(P, nvec, dim);
+    if (rot) {
+        H.rot_in.ensure(rot);
+        H.rot_out.ensure(rot);
     }
-    if (P.parts > 1) H.parts.ensure(parts_bytes(P, nvec, (uint64_t)1 << H.M));
+    void* parts = part ? H.parts.get(part, kMaxPartsBytes) : nullptr;
     ensure_diag(H, s);
-    launch_apply_impl(H, dtype, nvec, real_of_col, psi, out, P, s, two ? H.rot_in.p : nullptr,
-                      two ? H.rot_out.p : nullptr, P.parts > 1 ? H.parts.p : nullptr, true);
+    launch_apply_impl(H, dtype, nvec, real_of_col, psi, out, P, s, rot ? H.rot_in.p : nullptr,
+                      rot ? H.rot_out.p : nullptr, parts, true);
 }
 
 namespace {

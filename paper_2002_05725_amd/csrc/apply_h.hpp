@@ -74,6 +74,7 @@ struct ApplyPlan {
     int two_layouts; // also run the masks that flip few rows of a tile on a bit-rotated copy
     bool fixed_tile; // the tile was chosen by the caller
     int parts;       // > 1: the masks are split over this many workgroups per tile, whose sums a second kernel adds
+    int cut;         // the split its tables were cut for: parts, or another call's split whose tables serve this one
     int groups;      // the 16-row kernel with every QUAD mask in a group (tiles of 2^12 rows)
     int rot;         // two layouts: the second one's row bits are rotated right by this many
     int nc;          // columns per workgroup where a launch's columns pair up by realisation (1 or 2)

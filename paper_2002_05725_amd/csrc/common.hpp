@@ -3,10 +3,13 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
+#include <memory>
 #include <stdexcept>
 #include <string>
+#include <vector>
 
 #include "../../include/syk.h"
 
@@ -81,6 +84,24 @@ struct DevBuf {
 // has finished: after a launch or a wait that failed, the next use fills it again.
 struct TableBuf : DevBuf {
     bool ready = false;
+};
+
+// Scratch that grows but never moves what it gave out, so that launches captured
+// in a graph keep valid addresses: a buffer it has outgrown lives on with it.  Each
+// is at least twice the one before (up to `most`), so the old ones together are
+// no larger than the newest.
+struct KeptBuf {
+    std::vector<std::unique_ptr<DevBuf>> bufs;
+    size_t bytes() const { return bufs.empty() ? 0 : bufs.back()->bytes; }
+    void* get(size_t n, size_t most)
+    {
+        if (n > bytes()) {
+            std::unique_ptr<DevBuf> b(new DevBuf());
+            b->ensure(std::max(n, std::min(2 * bytes(), most)));
+            bufs.push_back(std::move(b));
+        }
+        return bufs.empty() ? nullptr : bufs.back()->p;
+    }
 };
 
 // Pinned host buffer owned by the library, read by the host after the stream

@@ -45,7 +45,7 @@ struct HamiltonianDev {
     // Coefficients of every mask and row of small states, per element type (filled on first use).
     mutable TableBuf table_d, table_f;
     // Partial sums of launches with their masks split over several workgroups per tile.
-    mutable DevBuf parts;
+    mutable KeptBuf parts;
     // The diagonal of H per realisation (FP64, [n_real][2^M]), filled on the
     // first apply: it does not depend on the state.
     mutable DevBuf diag;
