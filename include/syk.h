@@ -121,10 +121,13 @@ syk_status syk_apply_H_noalloc(syk_terms t, syk_dtype dtype, int nvec, const int
  * tiles, 0 keeps the hardware's round-robin order.  cols_per_group = 2 lets one
  * workgroup serve two consecutive columns of a block that share a realisation
  * (the two typical states of one disorder draw), decoding every mask once for
- * both; it needs tile_bits 10 or 11 (or automatic, where smaller tiles fall
- * back to one column), and a launch whose columns do not pair up by
- * realisation runs one column per workgroup.  1: one column per workgroup.
- * 0 (automatic): two for complex64, one for complex128.  The product is the
+ * both; it needs tile_bits 10 or 11 (or automatic, where states of at most
+ * 2^12 rows fall back to one column), and a launch whose columns do not pair
+ * up by realisation runs one column per workgroup.  1: one column per
+ * workgroup.  0: with a tile given, two for complex64 and one for complex128;
+ * with automatic tiles, two for complex64 blocks of 2^17 to 2^19 rows that fill
+ * the chip, where that is faster, and one elsewhere.  Automatic tiles have
+ * kernels of their own, with up to 16 rows per thread.  The product is the
  * same in every shape up to the order of floating-point sums (and bit for bit
  * between one and two columns per workgroup on the same tiles).  Other values give SYK_EINVAL and leave the setting
  * unchanged. */

@@ -1427,6 +1427,7 @@ ApplyPlan plan_apply(int M, int nvec, syk_dtype dtype, const ApplyTuning* tune, 
     int tb = std::min(M, 11);
     P.parts = 1;
     P.fixed_tile = tune && tune->tile_bits > 0;
+    P.cols = tune ? tune->cols : 0;
     if (P.fixed_tile) {
         tb = std::min(tune->tile_bits, M);
     } else {
@@ -1467,8 +1468,8 @@ ApplyPlan plan_apply(int M, int nvec, syk_dtype dtype, const ApplyTuning* tune, 
     // thread.  By default complex64 takes them: its 8-row kernel holds both
     // columns' sums at three waves per SIMD and decodes each mask once for
     // both; complex128 would drop to two waves per SIMD and gains nothing.
-    const bool explicit_cols = tune && tune->cols > 0;
-    P.nc = explicit_cols ? tune->cols : (dtype == SYK_C64 ? 2 : 1);
+    const bool explicit_cols = P.cols > 0;
+    P.nc = explicit_cols ? P.cols : (dtype == SYK_C64 ? 2 : 1);
     if (P.groups) P.nc = 1;
     if (P.nc == 2 && P.rpt < 4) {
         if (explicit_cols && tune->tile_bits > 0)
@@ -1495,19 +1496,22 @@ void launch_apply_impl(const HamiltonianDev& H, syk_dtype dtype, int nvec, const
                        void* parts, bool timed);
 }  // namespace
 
-// The plan of one call: complex64 blocks whose columns pair up by realisation,
-// 2^17 to 2^19 rows and enough columns to fill the chip, run two columns per
-// workgroup at 8 rows per thread (N=36, 32 columns: 3.65 ms against 3.75-3.97 with
-// the 16-row kernel, 64 columns: 7.30 against 7.42-7.50; N=38, 64 columns: 17.9
-// against 18.1).  Below, the 16-row kernel is faster (N=32: 1.23 against 1.50),
-// and from 2^20 rows on again (N=40, 64 columns: 43.4 against 44.3).
+// The plan of one call whose columns all pair up by realisation: two columns per
+// workgroup at 8 rows, if the caller asked for two, or for complex64 blocks of 2^17
+// to 2^19 rows with enough columns to fill the chip unless the caller asked for one
+// (N=36, 32 columns: 3.65 ms against 3.75-3.97 with the 16-row kernel, 64 columns:
+// 7.30 against 7.42-7.50; N=38, 64 columns: 17.9 against 18.1).  Below, the 16-row
+// kernel is faster (N=32: 1.23 against 1.50), and from 2^20 rows on again (N=40, 64
+// columns: 43.4 against 44.3).
 static ApplyPlan plan_of_call(const HamiltonianDev& H, const ApplyPlan& P, syk_dtype dtype, int nvec, const int32_t* real)
 {
-    if (!P.groups || P.parts > 1 || dtype != SYK_C64 || H.M < 17 || H.M > 19 || nvec % 2 != 0) return P;
+    if (!P.groups || nvec % 2 != 0 || P.cols == 1) return P;
+    if (P.cols != 2 && (P.parts > 1 || dtype != SYK_C64 || H.M < 17 || H.M > 19)) return P;
     for (int c = 0; real && c < nvec; c += 2)
         if (real[c] != real[c + 1]) return P;
-    const ApplyPlan Q = plan_apply(H.M, nvec, dtype, nullptr, false);
-    return Q.parts == 1 && Q.nc == 2 ? Q : P;
+    const ApplyTuning t{0, P.xcd_remap, P.cols};
+    const ApplyPlan Q = plan_apply(H.M, nvec, dtype, &t, false);
+    return Q.nc == 2 && (P.cols == 2 || Q.parts == 1) ? Q : P;
 }
 
 // Bytes of the partial sums of a split launch (FP64 for both state types): at

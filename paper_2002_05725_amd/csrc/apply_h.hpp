@@ -73,6 +73,7 @@ struct ApplyPlan {
     int xcd_remap;
     int two_layouts; // also run the masks that flip few rows of a tile on a bit-rotated copy
     bool fixed_tile; // the tile was chosen by the caller
+    int cols;        // columns per workgroup asked for by the caller (0: none)
     int parts;       // > 1: the masks are split over this many workgroups per tile, whose sums a second kernel adds
     int cut;         // the split its tables were cut for: parts, or another call's split whose tables serve this one
     int groups;      // the 16-row kernel with every QUAD mask in a group (tiles of 2^12 rows)

@@ -5,7 +5,8 @@
 // tables, wherever a plan that ties the tables to the tile alone could: for each
 // pair of calls the tables the first one builds are entered in the handle's maps
 // (empty: only their keys are read) and existing_route must find a route for the
-// second whose tables exist and whose scratch fits.
+// second whose tables exist and whose scratch fits.  The settings of a handle with
+// automatic tiles must reach the plan of every call.
 #include "apply_h.hip"
 
 #include <cstdio>
@@ -120,10 +121,36 @@ void check_routes()
     CHECK(!existing_route(H, plan_apply(16, 1, SYK_C128, &t), SYK_C128, 1, [](const ApplyPlan&) { return true; }, r), "other tile");
 }
 
+// The settings of syk_set_apply_tuning with automatic tiles reach the plan of every
+// call: one or two columns per workgroup as asked for, and the tile order.
+void check_tuning()
+{
+    for (int M = 13; M <= 23; ++M)
+        for (int dti = 0; dti < 2; ++dti)
+            for (int nvec : {1, 2, 7, 8, 16, 64, 66})
+                for (int xcd = 0; xcd < 2; ++xcd)
+                    for (int cols = 0; cols <= 2; ++cols)
+                        for (int paired = 0; paired < 2; ++paired) {
+                            const syk_dtype dt = dti ? SYK_C64 : SYK_C128;
+                            HamiltonianDev H;
+                            H.M = M;
+                            const ApplyTuning t{0, xcd, cols};
+                            const auto real = columns(nvec, paired);
+                            const ApplyPlan P = plan_of_call(H, plan_apply(M, nvec, dt, &t), dt, nvec, real.data());
+                            CHECK(P.xcd_remap == xcd, "M=%d nvec=%d cols=%d: tile order %d became %d", M, nvec, cols, xcd, P.xcd_remap);
+                            if (cols == 1) CHECK(P.nc == 1, "M=%d nvec=%d: one column per workgroup became %d", M, nvec, P.nc);
+                            if (cols == 2 && paired && nvec % 2 == 0)
+                                CHECK(P.nc == 2, "M=%d esz=%zu nvec=%d: two columns per workgroup became %d", M, elem_bytes(dt), nvec, P.nc);
+                            if (cols == 0 && nvec % 2 == 0 && paired && P.nc == 2)
+                                CHECK(dt == SYK_C64 && M >= 17 && M <= 19 && P.parts == 1, "M=%d: two columns outside their window", M);
+                        }
+}
+
 }  // namespace
 
 int main()
 {
+    check_tuning();
     check_routes();
     std::printf(bad ? "%d BAD\n" : "plan checks ok\n", bad);
     return bad != 0;

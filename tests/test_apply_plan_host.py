@@ -1,7 +1,8 @@
 """Host check of apply_H's launch choice, without a GPU (tests/host/apply_plan_check.cpp):
 after a product of one block width and pairing of its columns, a call that may
 build no tables finds a route for any other width and pairing that a rule tied to
-the tile alone would serve, within the scratch it has."""
+the tile alone would serve, within the scratch it has; and the columns per
+workgroup and tile order asked for with automatic tiles reach every plan."""
 import os
 import subprocess
 

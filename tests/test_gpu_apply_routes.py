@@ -2,7 +2,8 @@
 under graph capture run from the tables that an earlier product of another block
 width, or of columns that pair up otherwise, has built; and the routes of the
 allocation-free entry that give syk_apply_H's bits: two columns per workgroup,
-and the coefficient table of small states."""
+and the coefficient table of small states; and automatic tiles with the columns
+per workgroup and the tile order set by the caller."""
 import numpy as np
 import pytest
 import torch
@@ -110,4 +111,24 @@ def test_captured_product_outlives_wider_calls(N, warm, nvec, dtype):
         err = ((y - ref).norm(dim=-1) / ref.norm(dim=-1)).max().item()
         assert err <= TOL[dtype], k
         assert ((got - wref).norm(dim=-1) / wref.norm(dim=-1)).max().item() <= TOL[dtype]
+    T.close()
+
+
+@pytest.mark.parametrize("dtype", list(TOL))
+@pytest.mark.parametrize("N,nvec", [(20, 4), (26, 6), (32, 64), (36, 8)])
+def test_automatic_tiles_with_columns_asked_for(N, nvec, dtype):
+    """Two columns per workgroup on automatic tiles is the 2^11-row kernel (bit for
+    bit, where neither launch is split); one column and the other tile order
+    give the same product."""
+    x, real = _states(N, nvec, dtype), _cols(nvec, 1)
+    T = _handle(N)
+    ref = api.apply_H(T, x, real_of_col=real)
+    for xcd in (0, 1):
+        for cols in (1, 2):
+            api.set_apply_tuning(T, 0, xcd, cols)
+            y = api.apply_H(T, x, real_of_col=real)
+            assert ((y - ref).norm(dim=-1) / ref.norm(dim=-1)).max().item() <= TOL[dtype], (xcd, cols)
+    if (nvec << (N // 2)) >> 11 >= 1024:
+        api.set_apply_tuning(T, 11, 1, 2)
+        assert torch.equal(api.apply_H(T, x, real_of_col=real), y)
     T.close()
