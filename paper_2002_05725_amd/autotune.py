@@ -8,8 +8,9 @@ round robin) and, for blocks of an even number of columns, whether one
 workgroup serves two columns of one realisation (tile_bits 10 and 11).  Each candidate is timed with the library's HIP-event timing of
 apply_H on the handle's own tables for the requested block width and dtype,
 the fastest is installed on the handle, and the choice is cached in a JSON file
-keyed by (device architecture, N, dtype, block width), so a later run installs
-it without timing.
+keyed by (device architecture, library build, N, dtype, block width), so a later
+run of the same library installs it without timing and another build's kernels
+are timed anew.
 
 The library's automatic shape (which also has kernels of its own for small
 states and for tiles of 2^12 rows) is timed beside the candidates.
@@ -19,12 +20,14 @@ shapes that produce the same product (up to the order of FP64 row sums).
 """
 from __future__ import annotations
 
+import functools
+import hashlib
 import json
 import os
 
 import torch
 
-from . import api
+from . import _lib, api
 
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "paper_2002_05725_amd", "apply_tuning.json")
 
@@ -43,9 +46,23 @@ def candidates(N: int, nvec: int = 1) -> list[tuple[int, int, int]]:
     return out
 
 
+@functools.lru_cache(maxsize=None)
+def _build_id(path: str) -> str:
+    """A digest of the built library: what was fastest in one build need not be in another."""
+    with open(path, "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()[:16]
+
+
 def cache_key(arch: str, N: int, dtype: torch.dtype, nvec: int) -> str:
     name = {torch.complex128: "c128", torch.complex64: "c64"}[dtype]
-    return f"{arch}|N={N}|{name}|nvec={nvec}"
+    return f"{arch}|{_build_id(_lib.LIB_PATH)}|N={N}|{name}|nvec={nvec}"
+
+
+def cached_choice(path: str, key: str) -> dict | None:
+    """The cached entry of this key, if it holds the automatic shape's time beside
+    the candidates' (otherwise the automatic shape was never weighed: no entry)."""
+    hit = read_cache(path).get(key)
+    return hit if isinstance(hit, dict) and "automatic_ms" in hit else None
 
 
 def read_cache(path: str) -> dict:
@@ -103,7 +120,7 @@ def time_shape(terms: api.Terms, x: torch.Tensor, y: torch.Tensor, tile_bits: in
 
 def _install(terms: api.Terms, entry: dict) -> None:
     """Sets the entry's shape on the handle, or the automatic one if that was as fast."""
-    if entry.get("automatic_ms", float("inf")) <= entry["ms"]:
+    if entry["automatic_ms"] <= entry["ms"]:
         api.set_apply_tuning(terms, 0, 1, 0)
     else:
         api.set_apply_tuning(terms, entry["tile_bits"], entry["xcd_remap"], entry.get("cols_per_group", 1))
@@ -125,7 +142,7 @@ def tune_apply(terms: api.Terms, dtype: torch.dtype = torch.complex128, nvec: in
         raise ValueError("nvec and reps must be >= 1")
     key = cache_key(_arch(), terms.N, dtype, nvec)
     if cache and use_cache:
-        hit = read_cache(cache).get(key)
+        hit = cached_choice(cache, key)
         if hit is not None:
             _install(terms, hit)
             return hit
