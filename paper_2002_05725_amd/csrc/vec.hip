@@ -11,6 +11,7 @@
 #include <cstring>
 #include <type_traits>
 
+#include "sums.hpp"
 #include "vec.hpp"
 
 namespace syk {
@@ -164,11 +165,28 @@ void with_count(int k, F&& f)
     }
 }
 
+// Groups left after n of them are halved until at most 16 remain.
+constexpr int folded(int n) { return n <= 16 ? n : folded((n + 1) / 2); }
+
+// tmp[q N + i] += tmp[(q + h) N + i], h the upper half of the n groups, until at
+// most 16 remain.
+template <int N, int n>
+__device__ __forceinline__ void fold_groups(double* tmp, int t)
+{
+    if constexpr (n > 16) {
+        constexpr int h = (n + 1) / 2;
+        if (t < (n - h) * N) tmp[t] += tmp[t + h * N];
+        __syncthreads();
+        fold_groups<N, h>(tmp, t);
+    }
+}
+
 // Partial sums of a reduction of N doubles per column: [column][workgroup g < G][N].
 // Every workgroup of the kernel that uses the sums adds the G entries itself, in
-// a fixed order (256 / N strided groups, then the groups in order), or, for
-// large blocks, a finishing kernel has reduced them and G is 1 (kFusedRows).  The
-// result is in out[0..N) of LDS for every thread.
+// a fixed order (256 / N strided groups of four running sums each, then the groups
+// pairwise: one after another, the 256 of ||w||^2 at 2^16 rows had five times the
+// rounding error), or, for large blocks, a finishing kernel has reduced them and G
+// is 1 (kFusedRows).  The result is in out[0..N) of LDS for every thread.
 template <int N>
 __device__ __forceinline__ void sum_partials(const double* __restrict__ partial, int G, double (&tmp)[RB],
                                              double (&out)[N])
@@ -176,16 +194,18 @@ __device__ __forceinline__ void sum_partials(const double* __restrict__ partial,
     constexpr int kGroups = RB / N;
     const double* p = partial + (int64_t)blockIdx.y * G * N;
     const int t = threadIdx.x, i = t % N, q = t / N;
-    double s = 0.0;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
     if (q < kGroups)
-        for (int g = q; g < G; g += kGroups) s += p[(int64_t)g * N + i];
-    tmp[t] = s;
+        for (int g = q; g < G; g += 4 * kGroups) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (g + u * kGroups < G) s[u] += p[(int64_t)(g + u * kGroups) * N + i];
+        }
+    tmp[t] = (s[0] + s[1]) + (s[2] + s[3]);
     __syncthreads();
-    if (t < N) {
-        double o = tmp[t];
-        for (int k = 1; k < kGroups; ++k) o += tmp[k * N + t];
-        out[t] = o;
-    }
+    // halved in LDS down to at most 16 groups, which one thread per value adds
+    fold_groups<N, kGroups>(tmp, t);
+    if (t < N) out[t] = pairwise_sum<folded(kGroups)>(tmp + t, N);
     __syncthreads();
 }
 
@@ -477,24 +497,31 @@ __global__ void __launch_bounds__(kSmallThreads) k_lanczos_small(const cplx<R>* 
     for (int pass = 0; pass < 2; ++pass) {
         for (int k = wave; k < K; k += kSmallThreads / 64) {
             const cplx<R>* v = Vc + k * vstride;
-            // four running sums per lane: short chains of rounding errors
-            double a4[4] = {0.0, 0.0, 0.0, 0.0}, b4[4] = {0.0, 0.0, 0.0, 0.0};
-            auto add = [&](int r, int u) {
-                const cplx<R> x = v[r], y = ws[r];
-                const double vr = x.re, vi = x.im, br = y.re, bi = y.im;
-                a4[u] += vr * br + vi * bi;
-                b4[u] += vr * bi - vi * br;
-            };
-            if (D >= 256) {   // D is a power of two
+            // four running sums per lane and 1,024 rows: chains of at most four
+            // additions (of eight, 7% more rounding at 2,048 rows than a reduction
+            // over workgroups)
+            double ar = 0.0, ai = 0.0;
+            for (int h = 0; h < D; h += 1024) {
+                double a4[4] = {0.0, 0.0, 0.0, 0.0}, b4[4] = {0.0, 0.0, 0.0, 0.0};
+                auto add = [&](int r, int u) {
+                    const cplx<R> x = v[r], y = ws[r];
+                    const double vr = x.re, vi = x.im, br = y.re, bi = y.im;
+                    a4[u] += vr * br + vi * bi;
+                    b4[u] += vr * bi - vi * br;
+                };
+                const int end = min(D, h + 1024);
+                if (D >= 256) {   // D is a power of two
 #pragma unroll 2
-                for (int r = lane; r < D; r += 256) {
+                    for (int r = h + lane; r < end; r += 256) {
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) add(r + 64 * u, u);
+                        for (int u = 0; u < 4; ++u) add(r + 64 * u, u);
+                    }
+                } else {
+                    for (int r = lane; r < D; r += 64) add(r, 0);
                 }
-            } else {
-                for (int r = lane; r < D; r += 64) add(r, 0);
+                ar += (a4[0] + a4[1]) + (a4[2] + a4[3]);
+                ai += (b4[0] + b4[1]) + (b4[2] + b4[3]);
             }
-            double ar = (a4[0] + a4[1]) + (a4[2] + a4[3]), ai = (b4[0] + b4[1]) + (b4[2] + b4[3]);
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) {
                 ar += __shfl_xor(ar, off, 64);
@@ -529,8 +556,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_lanczos_small(const cplx<R>* 
     for (int off = 32; off > 0; off >>= 1) nrm += __shfl_xor(nrm, off, 64);
     if (lane == 0) red[wave] = nrm;
     __syncthreads();
-    double wn = 0.0;
-    for (int i = 0; i < kSmallThreads / 64; ++i) wn += red[i];
+    const double wn = pairwise_sum<kSmallThreads / 64>(red);
     const double f = lanczos_scalars(z, cs[0][2 * j] + cs[1][2 * j], wn, j, m, S.B, c, t == 0);
     if (j == m - 1) {
         __syncthreads();
@@ -589,9 +615,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_lanczos_build(const cplx<R>* 
         __syncthreads();
         if (lane == 0) red[wave] = v;
         __syncthreads();
-        double o = 0.0;
-        for (int i = 0; i < kW; ++i) o += red[i];
-        return o;
+        return pairwise_sum<kW>(red);
     };
     double n2 = 0.0;
     if (t < D) {
