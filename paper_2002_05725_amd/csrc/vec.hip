@@ -337,17 +337,28 @@ __global__ void __launch_bounds__(RB) k_update_dot(cplx<R>* __restrict__ w, cons
 
 // out[c][i] = sum of partial[c][g][i] over g < G, for i < n doubles: one wave
 // per output, lane l adding g = l, l + 64, ... in order, then a fixed butterfly
-// over the lanes (the same order on every run).
-__global__ void __launch_bounds__(64) k_finish(const double* __restrict__ partial, int G, int n,
+// over the lanes (the same order on every run).  Four outputs per workgroup: one
+// each was bound by dispatching them (120,000 outputs: 54 us, 18 with four).
+__global__ void __launch_bounds__(RB) k_finish(const double* __restrict__ partial, int G, int n, int64_t outputs,
                                                double* __restrict__ out)
 {
-    const int i = blockIdx.x;
-    const int64_t c = blockIdx.y;
+    const int64_t o = (int64_t)blockIdx.x * kWaves + (threadIdx.x >> 6);
+    if (o >= outputs) return;
+    const int64_t c = (uint32_t)o / (uint32_t)n;
+    const int i = (int)(o - c * n), lane = (int)(threadIdx.x & 63u);
     double s = 0.0;
-    for (int g = (int)threadIdx.x; g < G; g += 64) s += partial[(c * G + g) * n + i];
+    for (int g = lane; g < G; g += 64) s += partial[(c * G + g) * n + i];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (threadIdx.x == 0) out[c * n + i] = s;
+    if (lane == 0) out[o] = s;
+}
+
+void launch_finish(const double* partial, int G, int n, int nvec, double* out, hipStream_t st)
+{
+    const int64_t outputs = (int64_t)n * nvec;
+    hipLaunchKernelGGL(k_finish, dim3((unsigned)((outputs + kWaves - 1) / kWaves)), dim3(RB), 0, st, partial, G, n,
+                       outputs, out);
+    SYK_HIP(hipGetLastError());
 }
 
 // The scalars of one column at Lanczos iteration j, the same on every thread
@@ -812,18 +823,17 @@ VecOps::Sums VecOps::finished(const double* part, int G, int n, const char* slot
 {
     if (dim_ * nvec_ <= kFusedRows && G <= kMaxFusedGroups) return Sums{part, G};
     double* out = (double*)h_.ws.get(slot, (size_t)2 * kFusedMax * nvec_ * sizeof(double));
-    hipLaunchKernelGGL(k_finish, dim3(n, nvec_), dim3(64), 0, s_, part, G, n, out);
-    SYK_HIP(hipGetLastError());
+    launch_finish(part, G, n, nvec_, out, s_);
     return Sums{out, 1};
 }
 
-// <V_k | w> for k in [k0, k0 + kk) as partial sums in `slot` (kk <= kFusedMax).
-VecOps::Sums VecOps::dots(const void* V, int k0, int kk, const void* w, const std::string& slot)
+// <V_k | w> for k in [k0, k0 + kk) as partial sums in `slot` (kk <= kFusedMax),
+// which is sized for `most` vectors: no reallocation as a basis grows.
+VecOps::Sums VecOps::partial_dots(const void* V, int k0, int kk, const void* w, const std::string& slot, int most)
 {
     Shape S{dim_, nvec_};
     const dim3 g = reduce_grid();
-    // sized for a full chunk: no reallocation as a basis grows
-    double* part = (double*)h_.ws.get(slot, (size_t)g.x * kFusedMax * nvec_ * 2 * sizeof(double));
+    double* part = (double*)h_.ws.get(slot, (size_t)g.x * most * nvec_ * 2 * sizeof(double));
     const char* v = (const char*)V + (size_t)k0 * vec_bytes();
     const int64_t vs = dim_ * nvec_;
     with_count<kFusedMax>(kk, [&](auto kc) {
@@ -834,7 +844,13 @@ VecOps::Sums VecOps::dots(const void* V, int k0, int kk, const void* w, const st
             hipLaunchKernelGGL((k_multidot<float, K_>), g, dim3(RB), 0, s_, (const c64*)v, vs, (const c64*)w, S, part);
     });
     SYK_HIP(hipGetLastError());
-    return finished(part, (int)g.x, 2 * kk, (slot + "_f").c_str());
+    return Sums{part, (int)g.x};
+}
+
+VecOps::Sums VecOps::dots(const void* V, int k0, int kk, const void* w, const std::string& slot, int most)
+{
+    const Sums p = partial_dots(V, k0, kk, w, slot, most);
+    return finished(p.p, p.G, 2 * kk, (slot + "_f").c_str());
 }
 
 // w -= sum_k c_k V_k for k in [k0, k0 + kk), c the sums of p; with norm_slot,
@@ -843,7 +859,7 @@ VecOps::Sums VecOps::subtract(void* w, const void* V, int k0, int kk, Sums p, co
 {
     Shape S{dim_, nvec_};
     const dim3 g = reduce_grid();
-    double* part = norm_slot ? (double*)h_.ws.get(norm_slot, (size_t)g.x * kFusedMax * nvec_ * 2 * sizeof(double)) : nullptr;
+    double* part = norm_slot ? (double*)h_.ws.get(norm_slot, (size_t)g.x * nvec_ * 2 * sizeof(double)) : nullptr;
     const char* v = (const char*)V + (size_t)k0 * vec_bytes();
     const int64_t vs = dim_ * nvec_;
     with_count<kFusedMax>(kk, [&](auto kc) {
@@ -859,11 +875,11 @@ VecOps::Sums VecOps::subtract(void* w, const void* V, int k0, int kk, Sums p, co
 }
 
 // The first update and the second projection in one sweep (K <= kFusedMax).
-VecOps::Sums VecOps::subtract_dots(void* w, const void* V, int K, Sums p, const std::string& slot)
+VecOps::Sums VecOps::subtract_dots(void* w, const void* V, int K, Sums p, const std::string& slot, int most)
 {
     Shape S{dim_, nvec_};
     const dim3 g = reduce_grid();
-    double* part = (double*)h_.ws.get(slot, (size_t)g.x * kFusedMax * nvec_ * 2 * sizeof(double));
+    double* part = (double*)h_.ws.get(slot, (size_t)g.x * most * nvec_ * 2 * sizeof(double));
     const int64_t vs = dim_ * nvec_;
     with_count<kFusedMax>(K, [&](auto kc) {
         constexpr int K_ = decltype(kc)::value;
@@ -876,17 +892,25 @@ VecOps::Sums VecOps::subtract_dots(void* w, const void* V, int K, Sums p, const 
     return finished(part, (int)g.x, 2 * K, (slot + "_f").c_str());
 }
 
+// Up to kDirect results the finishing kernel writes them to pinned host memory
+// itself, which saves the copy; each is a store of its own over the host link, so
+// that many go through device memory (16 rows, 60,000 columns: 425 us written
+// directly by one workgroup each, 263 copied).
+constexpr size_t kDirect = 4096;
+
 std::vector<zd> VecOps::multidot(const void* V, int K, const void* w)
 {
     const size_t n = (size_t)K * nvec_;
-    double* host = (double*)h_.pinned.get(2 * n * sizeof(double));
+    const bool direct = 2 * n <= kDirect;
+    std::vector<double> copied(direct ? 0 : 2 * n);
+    double* host = direct ? (double*)h_.pinned.get(2 * n * sizeof(double)) : copied.data();
+    double* out = direct ? host : (double*)h_.ws.get("md_out", 2 * n * sizeof(double));
     for (int k0 = 0; k0 < K; k0 += kFusedMax) {
         const int kk = std::min(kFusedMax, K - k0);
-        Sums p = dots(V, k0, kk, w, "md_part");
-        hipLaunchKernelGGL(k_finish, dim3(2 * kk, nvec_), dim3(64), 0, s_, p.p, p.G, 2 * kk,
-                           host + 2 * (size_t)k0 * nvec_);
-        SYK_HIP(hipGetLastError());
+        const Sums p = partial_dots(V, k0, kk, w, "md_part", std::min(K, kFusedMax));
+        launch_finish(p.p, p.G, 2 * kk, nvec_, out + 2 * (size_t)k0 * nvec_, s_);
     }
+    if (!direct) SYK_HIP(hipMemcpyAsync(host, out, 2 * n * sizeof(double), hipMemcpyDeviceToHost, s_));
     SYK_HIP(hipStreamSynchronize(s_));
     std::vector<zd> res(n);
     for (int k0 = 0; k0 < K; k0 += kFusedMax) {   // host: [chunk][column][k]
@@ -962,7 +986,7 @@ LanczosScalars VecOps::lanczos_begin(const void* psi, void* V, int m)
 {
     const LanczosScalars z = lanczos_arrays(m);
     Shape S{dim_, nvec_};
-    const Sums n = dots(psi, 0, 1, psi, "gs_n");
+    const Sums n = dots(psi, 0, 1, psi, "gs_n", 1);
     const dim3 g = grid_of(S, false);
     if (dt_ == SYK_C128)
         hipLaunchKernelGGL(k_lanczos_start<double>, g, dim3(RB), 0, s_, (const c128*)psi, (c128*)V, n.p, n.G, m, S, z);
@@ -990,14 +1014,15 @@ void VecOps::lanczos_step(void* w, void* V, int j, int m, const LanczosScalars& 
     // k0: the chunk that holds the newest vector
     const int nch = (K + kFusedMax - 1) / kFusedMax, k0 = (nch - 1) * kFusedMax, kl = K - k0;
     auto count = [&](int i) { return std::min(kFusedMax, K - i * kFusedMax); };
+    auto most = [&](int i) { return std::min(kFusedMax, m - i * kFusedMax); };   // ... in the last iteration
     auto slot = [](const char* s, int i) { return s + std::to_string(i); };
     std::vector<Sums> p1(nch), p2(nch);
-    for (int i = 0; i < nch; ++i) p1[i] = dots(V, i * kFusedMax, count(i), w, slot("gs_p", i));
+    for (int i = 0; i < nch; ++i) p1[i] = dots(V, i * kFusedMax, count(i), w, slot("gs_p", i), most(i));
     if (nch == 1) {
-        p2[0] = subtract_dots(w, V, K, p1[0], "gs_q0");
+        p2[0] = subtract_dots(w, V, K, p1[0], "gs_q0", most(0));
     } else {
         for (int i = 0; i < nch; ++i) subtract(w, V, i * kFusedMax, count(i), p1[i], nullptr);
-        for (int i = 0; i < nch; ++i) p2[i] = dots(V, i * kFusedMax, count(i), w, slot("gs_q", i));
+        for (int i = 0; i < nch; ++i) p2[i] = dots(V, i * kFusedMax, count(i), w, slot("gs_q", i), most(i));
     }
     Sums n{};
     for (int i = 0; i < nch; ++i) n = subtract(w, V, i * kFusedMax, count(i), p2[i], i == nch - 1 ? "gs_n" : nullptr);

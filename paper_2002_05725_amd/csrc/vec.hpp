@@ -78,9 +78,10 @@ private:
     bool small_lanczos(int m) const;
     LanczosScalars lanczos_arrays(int m);
     Sums finished(const double* part, int G, int n, const char* slot);
-    Sums dots(const void* V, int k0, int kk, const void* w, const std::string& slot);
+    Sums partial_dots(const void* V, int k0, int kk, const void* w, const std::string& slot, int most);
+    Sums dots(const void* V, int k0, int kk, const void* w, const std::string& slot, int most);
     Sums subtract(void* w, const void* V, int k0, int kk, Sums p, const char* norm_slot);
-    Sums subtract_dots(void* w, const void* V, int K, Sums p, const std::string& slot);
+    Sums subtract_dots(void* w, const void* V, int K, Sums p, const std::string& slot, int most);
 };
 
 }  // namespace syk
