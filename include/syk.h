@@ -137,7 +137,10 @@ syk_status syk_set_apply_tuning(syk_terms t, int tile_bits, int xcd_remap, int c
  * vectors, Chebyshev stacks, checkpoints, rotated-layout copies of the
  * gradient), in bytes; 0 removes the cap (the default).  A call that would
  * grow the workspace beyond the cap returns SYK_ENOMEM before allocating and
- * leaves the handle valid.  Lowering the cap does not free what is held. */
+ * leaves the handle valid.  Lowering the cap does not free what is held.  A
+ * handle with a cap takes the reductions that need the least room (the same
+ * results up to the order of sums).  Not counted: the coupling and launch tables
+ * and apply_H's own scratch. */
 syk_status syk_set_workspace_limit(syk_terms t, uint64_t bytes);
 
 /* Kernel timing: while enabled, every apply_H call records a HIP event before

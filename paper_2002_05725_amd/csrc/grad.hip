@@ -798,11 +798,14 @@ void grad_bins(syk_terms_s& h, const std::vector<const void*>& g, const std::vec
     // too, up to the workgroups the chip holds (each walks its pairs in series, two
     // per stage, and every stage waits for a round trip to memory).  Kernel time
     // with 32 pairs, us, before -> split: N=20 229 -> 77, N=24 255 -> 164; from N=28
-    // on one group (twice or four times as many workgroups: N=24 +10% / +30%).
+    // on one group (twice or four times as many workgroups: N=24 +10% / +30%).  Each
+    // group has its own slices of the bins, up to sixteen times the one group's at
+    // N=20: a handle with a workspace cap keeps to one.
     const int np = (npairs + kGradPairsPerStage - 1) / kGradPairsPerStage * kGradPairsPerStage;
     const uint32_t wg = L.tile_groups * L.chunk_groups;
     L.pair_groups = std::min<uint32_t>((uint32_t)(np / kGradPairsPerStage), std::max<uint32_t>(1u, kGradFill / wg));
     L.pair_groups = std::max<uint32_t>(1u, std::min<uint32_t>(L.pair_groups, 512u / L.tile_groups));
+    if (h.ws.limit > 0) L.pair_groups = 1;
     const int slices = nblk * (int)L.pair_groups;
 
     // rotated copies of the pair vectors for the masks of the second layout

@@ -808,20 +808,31 @@ void VecOps::majorana_sector(int a, int top, int s_in, const void* in, void* out
 // to stream at HBM speed and there a finishing launch is less than every
 // workgroup's own sum (64 complex64 columns at N=36: 134.4 ms a step without it,
 // 133.6 with).
+// A handle with a workspace cap runs the finishing kernel at every size: its partial
+// sums are used up at once and share one buffer, where the others are kept per 16
+// basis vectors (up to 2% of a basis, which a cap may not leave).
 constexpr int kMaxFusedGroups = 256;
 constexpr int64_t kFusedRows = (int64_t)1 << 18;
+
+bool VecOps::fused() const { return dim_ * nvec_ <= kFusedRows && h_.ws.limit == 0; }
+
+// The buffer of a reduction's partial sums.
+double* VecOps::part_buffer(const std::string& slot, size_t doubles)
+{
+    return (double*)h_.ws.get(fused() ? slot : "gs_part", doubles * sizeof(double));
+}
 
 dim3 VecOps::reduce_grid() const
 {
     Shape S{dim_, nvec_};
     dim3 g = grid_of(S, true);
-    if (dim_ * nvec_ <= kFusedRows && g.x > (unsigned)kMaxFusedGroups) g.x = kMaxFusedGroups;
+    if (fused() && g.x > (unsigned)kMaxFusedGroups) g.x = kMaxFusedGroups;
     return g;
 }
 
 VecOps::Sums VecOps::finished(const double* part, int G, int n, const char* slot)
 {
-    if (dim_ * nvec_ <= kFusedRows && G <= kMaxFusedGroups) return Sums{part, G};
+    if (fused()) return Sums{part, G};
     double* out = (double*)h_.ws.get(slot, (size_t)2 * kFusedMax * nvec_ * sizeof(double));
     launch_finish(part, G, n, nvec_, out, s_);
     return Sums{out, 1};
@@ -833,7 +844,7 @@ VecOps::Sums VecOps::partial_dots(const void* V, int k0, int kk, const void* w, 
 {
     Shape S{dim_, nvec_};
     const dim3 g = reduce_grid();
-    double* part = (double*)h_.ws.get(slot, (size_t)g.x * most * nvec_ * 2 * sizeof(double));
+    double* part = part_buffer(slot, (size_t)g.x * most * nvec_ * 2);
     const char* v = (const char*)V + (size_t)k0 * vec_bytes();
     const int64_t vs = dim_ * nvec_;
     with_count<kFusedMax>(kk, [&](auto kc) {
@@ -859,7 +870,7 @@ VecOps::Sums VecOps::subtract(void* w, const void* V, int k0, int kk, Sums p, co
 {
     Shape S{dim_, nvec_};
     const dim3 g = reduce_grid();
-    double* part = norm_slot ? (double*)h_.ws.get(norm_slot, (size_t)g.x * nvec_ * 2 * sizeof(double)) : nullptr;
+    double* part = norm_slot ? part_buffer(norm_slot, (size_t)g.x * nvec_ * 2) : nullptr;
     const char* v = (const char*)V + (size_t)k0 * vec_bytes();
     const int64_t vs = dim_ * nvec_;
     with_count<kFusedMax>(kk, [&](auto kc) {
@@ -879,7 +890,7 @@ VecOps::Sums VecOps::subtract_dots(void* w, const void* V, int K, Sums p, const 
 {
     Shape S{dim_, nvec_};
     const dim3 g = reduce_grid();
-    double* part = (double*)h_.ws.get(slot, (size_t)g.x * most * nvec_ * 2 * sizeof(double));
+    double* part = part_buffer(slot, (size_t)g.x * most * nvec_ * 2);
     const int64_t vs = dim_ * nvec_;
     with_count<kFusedMax>(K, [&](auto kc) {
         constexpr int K_ = decltype(kc)::value;

@@ -74,6 +74,8 @@ private:
         const double* p;
         int G;
     };
+    bool fused() const;
+    double* part_buffer(const std::string& slot, size_t doubles);
     dim3 reduce_grid() const;
     bool small_lanczos(int m) const;
     LanczosScalars lanczos_arrays(int m);
