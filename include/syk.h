@@ -125,7 +125,7 @@ syk_status syk_apply_H_noalloc(syk_terms t, syk_dtype dtype, int nvec, const int
  * 2^12 rows fall back to one column), and a launch whose columns do not pair
  * up by realisation runs one column per workgroup.  1: one column per
  * workgroup.  0: with a tile given, two for complex64 and one for complex128;
- * with automatic tiles, two for complex64 blocks of 2^17 to 2^19 rows that fill
+ * with automatic tiles, two for complex64 blocks of 2^18 and 2^19 rows that fill
  * the chip, where that is faster, and one elsewhere.  Automatic tiles have
  * kernels of their own, with up to 16 rows per thread.  The product is the
  * same in every shape up to the order of floating-point sums (and bit for bit

@@ -1416,14 +1416,15 @@ ApplyPlan plan_apply(int M, int nvec, syk_dtype dtype, const ApplyTuning* tune, 
     P.slices = (nvec + kColsPerLaunch - 1) / kColsPerLaunch;
     // 2048-row source tiles (256 threads, 8 rows each).  Where the tiles and
     // columns of a launch are fewer than kSplitGroups (four workgroups on each
-    // of the 256 CUs), the masks are split over several workgroups per tile:
-    // up to there the full tile's arithmetic per mask is worth more than the
-    // partial sums cost (16 B written and read per row and part).  One column,
-    // complex128, us per call, smaller tiles without a split (before) -> split:
-    // N=24 127 -> 16, N=32 383 -> 62, N=36 771 -> 261, N=40 2450 -> 1400; half
-    // or twice the number of workgroups: N=32 67 / 70, N=40 1705 / 1351.  More
-    // than 64 parts leave too few masks each (N=28: 28.0 with 64, 32.1 with 128).
-    // A shape given by the caller is run as it is given, unsplit.
+    // of the 256 CUs), the masks are split over several workgroups per tile, at most
+    // kMaxParts of them: up to there the full tile's arithmetic per mask is worth
+    // more than the partial sums cost (16 B written and read per row and part).
+    // Automatic plans come here with at most 2^12 rows (more run the 16-row kernel)
+    // and too many columns or realisations for the coefficient table, or with two
+    // columns per workgroup; us per call in complex128, smaller tiles unsplit ->
+    // split: N=20 64 columns 67 -> 25, N=22 16 columns 89 -> 31, 64 columns 107 -> 38,
+    // N=24 8 columns 129 -> 34, 64 columns 166 -> 63.  A shape given by the caller is
+    // run as it is given, unsplit.
     int tb = std::min(M, 11);
     P.parts = 1;
     P.fixed_tile = tune && tune->tile_bits > 0;
@@ -1480,10 +1481,10 @@ ApplyPlan plan_apply(int M, int nvec, syk_dtype dtype, const ApplyTuning* tune, 
     // whole tile from global memory; with at least C(7,4) of them, run the
     // masks that sit better in the rotated layout there.  A split launch is
     // short enough that the second layout's launches (two transposes, another
-    // product and sum) weigh more: from C(8,4) on (N=36: 261 us with one layout,
-    // 283 with two; N=38: 583 both; N=34, where C(6,4): 120 with one, 146 with two).
-    // The 16-row kernel unsplit: from C(6,4) on (64 complex64 columns at N=36: 7.29 ms
-    // with two layouts, 7.45 with one).
+    // product and sum) weigh more: from C(8,4) on (16-row kernel, one column, us,
+    // one layout / two: N=36 complex128 190 / 199, complex64 147 / 165; N=38 430 /
+    // 438, 324 / 330; N=40 1095 / 1052, 785 / 744).  The 16-row kernel unsplit: from
+    // C(6,4) on (64 complex64 columns at N=36: 7.29 ms with two layouts, 7.45 with one).
     P.two_layouts = (M - tb >= (P.parts > 1 ? 8 : P.groups ? 6 : 7) && tb >= 8) ? 1 : 0;
     P.rot = P.groups ? M - tb : tb;
     P.cut = P.parts;
@@ -1497,21 +1498,26 @@ void launch_apply_impl(const HamiltonianDev& H, syk_dtype dtype, int nvec, const
 }  // namespace
 
 // The plan of one call whose columns all pair up by realisation: two columns per
-// workgroup at 8 rows, if the caller asked for two, or for complex64 blocks of 2^17
-// to 2^19 rows with enough columns to fill the chip unless the caller asked for one
-// (N=36, 32 columns: 3.65 ms against 3.75-3.97 with the 16-row kernel, 64 columns:
-// 7.30 against 7.42-7.50; N=38, 64 columns: 17.9 against 18.1).  Below, the 16-row
-// kernel is faster (N=32: 1.23 against 1.50), and from 2^20 rows on again (N=40, 64
-// columns: 43.4 against 44.3).
+// workgroup at 8 rows, if the caller asked for two, or for complex64 blocks of 2^18
+// and 2^19 rows with at least kPairGroups workgroups unless the caller asked for one
+// (ms, 16-row kernel -> two columns: N=36 32 columns 3.76 -> 3.65, 64 columns 7.43 ->
+// 7.30; N=38 16 columns 4.64 -> 4.57, 64 columns 18.1 -> 17.9).  With half the
+// workgroups it is slower (N=36 16 columns 1.89 -> 2.23, N=38 8 columns 2.33 -> 2.76),
+// and so it is on smaller and larger states at every width (N=32 64 columns 1.17 ->
+// 1.44, N=34 2.96 -> 3.06, N=40 43.5 -> 44.6).
+constexpr int64_t kPairGroups = 2048;
+
 static ApplyPlan plan_of_call(const HamiltonianDev& H, const ApplyPlan& P, syk_dtype dtype, int nvec, const int32_t* real)
 {
     if (!P.groups || nvec % 2 != 0 || P.cols == 1) return P;
-    if (P.cols != 2 && (P.parts > 1 || dtype != SYK_C64 || H.M < 17 || H.M > 19)) return P;
+    if (P.cols != 2 && (dtype != SYK_C64 || H.M < 18 || H.M > 19 ||
+                        ((int64_t)1 << (H.M - 11)) * (std::min(nvec, kColsPerLaunch) / 2) < kPairGroups))
+        return P;
     for (int c = 0; real && c < nvec; c += 2)
         if (real[c] != real[c + 1]) return P;
     const ApplyTuning t{0, P.xcd_remap, P.cols};
     const ApplyPlan Q = plan_apply(H.M, nvec, dtype, &t, false);
-    return Q.nc == 2 && (P.cols == 2 || Q.parts == 1) ? Q : P;
+    return Q.nc == 2 ? Q : P;
 }
 
 // Bytes of the partial sums of a split launch (FP64 for both state types): at

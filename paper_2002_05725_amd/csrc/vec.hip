@@ -487,7 +487,11 @@ __global__ void __launch_bounds__(RB) k_lanczos_next(const cplx<R>* __restrict__
 // A projection is one wave's work (its lanes over the rows, one butterfly), an
 // update one thread per row; both read the basis from L2.  Bound by one CU's
 // read rate (four reads of the basis, (j + 1) x 16 KiB each at 1,024 complex128
-// rows), which up to 2,048 rows is less than four launches of ~5 us.
+// rows), against the sweeps' launches (four of ~5 us up to 16 vectors, four more
+// per further 16).  us per step, sweeps -> one launch an iteration: 512 rows m=20
+// 499 -> 319; 1,024 rows m=20 503 -> 372, m=64 2,620 -> 1,890, m=200 24,900 ->
+// 15,600; 2,048 rows m=20 541 -> 502, m=40 1,370 -> 1,350, 64 columns 2,390 ->
+// 2,230, and past the line there m=64 2,840 -> 2,930, m=200 25,700-27,200 -> 27,900.
 constexpr int kSmallRows = 2048, kSmallThreads = 1024, kSmallMaxM = 512;
 
 template <typename R>

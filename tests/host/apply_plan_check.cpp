@@ -127,7 +127,7 @@ void check_tuning()
 {
     for (int M = 13; M <= 23; ++M)
         for (int dti = 0; dti < 2; ++dti)
-            for (int nvec : {1, 2, 7, 8, 16, 64, 66})
+            for (int nvec : {1, 2, 7, 8, 14, 16, 30, 32, 64, 66})
                 for (int xcd = 0; xcd < 2; ++xcd)
                     for (int cols = 0; cols <= 2; ++cols)
                         for (int paired = 0; paired < 2; ++paired) {
@@ -141,8 +141,11 @@ void check_tuning()
                             if (cols == 1) CHECK(P.nc == 1, "M=%d nvec=%d: one column per workgroup became %d", M, nvec, P.nc);
                             if (cols == 2 && paired && nvec % 2 == 0)
                                 CHECK(P.nc == 2, "M=%d esz=%zu nvec=%d: two columns per workgroup became %d", M, elem_bytes(dt), nvec, P.nc);
-                            if (cols == 0 && nvec % 2 == 0 && paired && P.nc == 2)
-                                CHECK(dt == SYK_C64 && M >= 17 && M <= 19 && P.parts == 1, "M=%d: two columns outside their window", M);
+                            // unasked, two columns only where they are faster: complex64, 2^18 and 2^19
+                            // rows, at least 2048 workgroups
+                            const bool two = dt == SYK_C64 && (M == 18 || M == 19) && nvec % 2 == 0 && paired &&
+                                             (1 << (M - 11)) * (std::min(nvec, 64) / 2) >= 2048;
+                            if (cols == 0) CHECK(P.nc == (two ? 2 : 1), "M=%d nvec=%d paired=%d: %d columns per workgroup", M, nvec, paired, P.nc);
                         }
 }
 

@@ -45,8 +45,11 @@ CASES = [(20, 1, 0, 16, 0), (20, 33, 0, 4, 0), (24, 1, 0, 64, 0), (24, 8, 0, 1, 
          (38, 8, 1, 4, 0)]
 
 
-@pytest.mark.parametrize("dtype", list(TOL))
-@pytest.mark.parametrize("N,na,pa,nb,pb", CASES)
+# paired complex64 blocks wide enough for two columns per workgroup
+PAIRED = [(36, 32, 0, 32, 1), (38, 16, 0, 16, 1), (38, 16, 1, 4, 0)]
+
+
+@pytest.mark.parametrize("N,na,pa,nb,pb,dtype", [c + (d,) for d in TOL for c in CASES] + [c + (torch.complex64,) for c in PAIRED])
 def test_noalloc_after_another_width_or_pairing(N, na, pa, nb, pb, dtype):
     x, real = _states(N, nb, dtype), _cols(nb, pb)
     ref = _ref(N, x, real)
@@ -61,6 +64,7 @@ def test_noalloc_after_another_width_or_pairing(N, na, pa, nb, pb, dtype):
 
 
 @pytest.mark.parametrize("N,nvec,paired,dtype", [(36, 8, 1, torch.complex64), (36, 8, 0, torch.complex64),
+                                                 (36, 32, 1, torch.complex64), (38, 16, 1, torch.complex64),
                                                  (16, 1, 0, torch.complex128), (20, 5, 0, torch.complex64),
                                                  (24, 1, 0, torch.complex128), (24, 6, 0, torch.complex128),
                                                  (4, 3, 0, torch.complex128)])
