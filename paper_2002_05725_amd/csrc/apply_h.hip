@@ -1437,13 +1437,14 @@ ApplyPlan plan_apply(int M, int nvec, syk_dtype dtype, const ApplyTuning* tune, 
     }
     // 8 lane bits; a thread owns 2^(tile_bits - 8) rows, at most 8
     if (tb > kLaneBits + kMaxKBits) throw Error(SYK_EINVAL, "apply_H: tile_bits above 11");
-    // From 2^13 rows on the 16-row kernel with tiles of 2^12 rows (one complex128
-    // column, us, 8 rows -> 16: N=26 20 -> 18, N=32 62 -> 48, N=36 254 -> 218, N=44 7176 ->
-    // 5700; complex64 N=32 47 -> 42, N=44 4613 -> 4120; an exception in plan_of_call).  Its
-    // split fills the 512 workgroups the chip holds (two per CU): the parts that
-    // cost the fewest rounds of them, each part weighed with the 128 KiB its sums
-    // write and read per workgroup (N=32: 48 us with 32 parts, 61 with 64; seven
-    // columns: 246 with nine parts, 279 with five, whose last round is part-full).
+    // From 2^13 rows on the 16-row kernel with tiles of 2^12 rows (one column, us, 8
+    // rows -> 16: complex128 N=26 19.7 -> 17.4, N=32 55 -> 42, N=36 237 -> 192, N=44
+    // 7250 -> 5790; complex64 N=32 44 -> 39, N=44 4665 -> 4127; an exception in
+    // plan_of_call).  Its split fills the 512 workgroups the chip holds (two per CU):
+    // the parts that cost the fewest rounds of them, each part weighed with the
+    // 128 KiB its sums write and read per workgroup (N=32 complex128: 42 us with 31
+    // parts, 51 with 24, 53 with 64; seven columns: 195 with nine, 244 with five,
+    // whose last round is part-full).
     P.groups = allow_groups && !P.fixed_tile && M > kGroupTileBits;
     if (P.groups) {
         tb = kGroupTileBits;
