@@ -100,18 +100,21 @@ void build_tables(int N, int n_real, const double* J, TermTables& T)
             rec.type_tab = (uint32_t)MASK_QUAD << 28 | (uint32_t)T.n_quad;
             // T[idx]: idx bit m = bit q_m of the output row r; the source row
             // s = r ^ x has the opposite bits there.
-            for (int r = 0; r < n_real; ++r)
+            for (int r = 0; r < n_real; ++r) {
+                std::complex<double> cf[16];
+                for (int u = 0; u < 16; ++u) cf[u] = coef(ts[u], r);
                 for (int idx = 0; idx < 16; ++idx) {
                     uint32_t s_loc = 0;
                     for (int m = 0; m < 4; ++m)
                         if (!((idx >> m) & 1)) s_loc |= 1u << q[m];
                     std::complex<double> acc = 0.0;
-                    for (const Term& t : ts) {
-                        double sg = (__builtin_popcount(s_loc & t.p.z) & 1) ? -1.0 : 1.0;
-                        acc += sg * coef(t, r);
+                    for (int u = 0; u < 16; ++u) {
+                        double sg = (__builtin_popcount(s_loc & ts[u].p.z) & 1) ? -1.0 : 1.0;
+                        acc += sg * cf[u];
                     }
                     T.tab4.push_back({acc.real(), acc.imag()});
                 }
+            }
             T.qinfo.push_back(rec.qpack);
             T.qinfo.push_back(rec.zbase);
             ++T.n_quad;
