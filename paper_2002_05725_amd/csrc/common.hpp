@@ -109,6 +109,7 @@ struct KeptBuf {
 struct PinnedBuf {
     void* p = nullptr;
     size_t bytes = 0;
+    int asked = 0;
     PinnedBuf() = default;
     PinnedBuf(const PinnedBuf&) = delete;
     PinnedBuf& operator=(const PinnedBuf&) = delete;
@@ -135,6 +136,10 @@ struct PinnedBuf {
         bytes = n;
         return p;
     }
+    // The buffer, or NULL for the first four requests it would have to grow for:
+    // allocating it takes 70 us, a copy from device memory instead 9, and a handle
+    // may be used only once or twice.
+    void* get_if_used(size_t n) { return n > bytes && asked++ < 4 ? nullptr : get(n); }
 };
 
 }  // namespace syk

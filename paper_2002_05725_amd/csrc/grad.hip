@@ -599,10 +599,10 @@ void couplings_from_bins(syk_terms_s& h, const double* bins_dev, double* out, hi
     const size_t n = T.terms.size();
     // one buffer: the results, the couplings' references, the masks' bin offsets
     const size_t rb = n * sizeof(double), tb = n * sizeof(TermRef), ob = T.bin_off.size() * sizeof(uint32_t);
-    // From a handle's second call on the kernel writes pinned host memory itself (N=16,
-    // 72 us a call against 81 with a copy); a handle used once does not pay for
-    // allocating it (70 us: N=16 built, used once and closed 425 us against 500).
-    const bool pinned = h.term_refs.ready || h.pinned.bytes >= rb;
+    // The kernel writes pinned host memory itself (N=16: 72 us a call, 81 with a copy),
+    // but a handle used once does not pay for allocating it (N=16 built, used once and
+    // closed: 425 us, 500 with it).
+    double* host = static_cast<double*>(h.pinned.get_if_used(rb));
     if (!h.term_refs.ready) {   // once per handle; finished before use on any stream
         std::vector<char> up(tb + ob);
         std::memcpy(up.data(), T.terms.data(), tb);
@@ -613,7 +613,6 @@ void couplings_from_bins(syk_terms_s& h, const double* bins_dev, double* out, hi
         h.term_refs.ready = true;
     }
     double* res = h.term_refs.as<double>();
-    double* host = pinned ? static_cast<double*>(h.pinned.get(rb)) : nullptr;
     const TermRef* tr = reinterpret_cast<const TermRef*>(res + n);
     hipLaunchKernelGGL(k_couplings, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, tr, h.H.masks,
                        reinterpret_cast<const uint32_t*>(tr + n), bins_dev, (uint32_t)n, host ? host : res);

@@ -916,9 +916,10 @@ constexpr size_t kDirect = 4096;
 std::vector<zd> VecOps::multidot(const void* V, int K, const void* w)
 {
     const size_t n = (size_t)K * nvec_;
-    const bool direct = 2 * n <= kDirect;
+    double* host = 2 * n <= kDirect ? (double*)h_.pinned.get_if_used(2 * n * sizeof(double)) : nullptr;
+    const bool direct = host != nullptr;
     std::vector<double> copied(direct ? 0 : 2 * n);
-    double* host = direct ? (double*)h_.pinned.get(2 * n * sizeof(double)) : copied.data();
+    if (!direct) host = copied.data();
     double* out = direct ? host : (double*)h_.ws.get("md_out", 2 * n * sizeof(double));
     for (int k0 = 0; k0 < K; k0 += kFusedMax) {
         const int kk = std::min(kFusedMax, K - k0);
