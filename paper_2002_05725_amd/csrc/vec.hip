@@ -918,17 +918,21 @@ std::vector<zd> VecOps::multidot(const void* V, int K, const void* w)
     const size_t n = (size_t)K * nvec_;
     double* host = 2 * n <= kDirect ? (double*)h_.pinned.get_if_used(2 * n * sizeof(double)) : nullptr;
     const bool direct = host != nullptr;
-    std::vector<double> copied(direct ? 0 : 2 * n);
-    if (!direct) host = copied.data();
     double* out = direct ? host : (double*)h_.ws.get("md_out", 2 * n * sizeof(double));
     for (int k0 = 0; k0 < K; k0 += kFusedMax) {
         const int kk = std::min(kFusedMax, K - k0);
         const Sums p = partial_dots(V, k0, kk, w, "md_part", std::min(K, kFusedMax));
         launch_finish(p.p, p.G, 2 * kk, nvec_, out + 2 * (size_t)k0 * nvec_, s_);
     }
-    if (!direct) SYK_HIP(hipMemcpyAsync(host, out, 2 * n * sizeof(double), hipMemcpyDeviceToHost, s_));
-    SYK_HIP(hipStreamSynchronize(s_));
+    // host memory for the results while the kernels run; one vector's are in order already
     std::vector<zd> res(n);
+    std::vector<double> copied(direct || K == 1 ? 0 : 2 * n);
+    if (!direct) {
+        host = K == 1 ? reinterpret_cast<double*>(res.data()) : copied.data();
+        SYK_HIP(hipMemcpyAsync(host, out, 2 * n * sizeof(double), hipMemcpyDeviceToHost, s_));
+    }
+    SYK_HIP(hipStreamSynchronize(s_));
+    if (!direct && K == 1) return res;
     for (int k0 = 0; k0 < K; k0 += kFusedMax) {   // host: [chunk][column][k]
         const int kk = std::min(kFusedMax, K - k0);
         const double* h = host + 2 * (size_t)k0 * nvec_;
