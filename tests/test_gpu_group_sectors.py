@@ -1,5 +1,5 @@
 """The 16-row apply kernel on parity-sector states, unsplit with two row layouts
-(2^18 to 2^20 rows), against the checker on sampled rows of the full space; several
+(2^18 to 2^20 rows), against the oracle on sampled rows of the full space; several
 columns of two realisations, both precisions."""
 import numpy as np
 import pytest
@@ -13,7 +13,7 @@ DEV = torch.device("cuda:0")
 
 
 @pytest.mark.parametrize("N,sector,nvec", [(38, 0, 9), (38, 1, 16), (40, 1, 5), (42, 0, 3)])
-def test_sector_rows_match_checker(N, sector, nvec):
+def test_sector_rows_match_oracle(N, sector, nvec):
     M = N // 2
     Js = np.stack([inputs.couplings(N, 80 + r) for r in range(2)])
     real = np.array([c % 2 for c in range(nvec)], dtype=np.int32)
