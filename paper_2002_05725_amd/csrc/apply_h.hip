@@ -20,6 +20,7 @@
 // to every column.  Up to 64 columns per launch.
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -976,11 +977,11 @@ void launch_groups(const HamiltonianDev& H, const KTerms<R>& T, const Hamiltonia
 {
     auto* in = static_cast<const cplx<R>*>(psi);
     auto* o = static_cast<cplx<R>*>(out);
-    const auto* ch = A.chunks.as<GroupChunk>();
-    const auto* gr = A.groups.as<GroupRec>();
-    const auto* tb = A.tables.as<cplx<R>>();
+    const auto* ch = static_cast<const GroupChunk*>(A.chunks);
+    const auto* gr = static_cast<const GroupRec*>(A.groups);
+    const auto* tb = static_cast<const cplx<R>*>(A.tables);
     const auto* pt = (sizeof(R) == 8 ? H.pair_tab_d : H.pair_tab_f).as<cplx<R>>();
-    const auto* pr = A.pairs.as<PairRec>();
+    const auto* pr = static_cast<const PairRec*>(A.pairs);
     const dim3 grid(L.n_tiles, ncols, L.n_parts), block(256);
     if (L.n_parts > 1) hipLaunchKernelGGL((k_apply_groups<R, true>), grid, block, 0, s, T, ch, gr, tb, pt, pr, L, in, o, parts);
     else hipLaunchKernelGGL((k_apply_groups<R, false>), grid, block, 0, s, T, ch, gr, tb, pt, pr, L, in, o, parts);
@@ -1307,6 +1308,34 @@ std::vector<MaskRec> group_layout_masks(const std::vector<MaskRec>& masks, int M
     return out;
 }
 
+// Tables of a launch in one allocation and one upload: a handle's first product is
+// mostly these (N=26, five complex64 columns, beside other handles: 290 us, 360 with
+// an allocation and a copy for each).
+struct TablePack {
+    std::vector<char> host;
+    size_t room(size_t n)   // of n bytes (at least 64), its offset
+    {
+        const size_t o = (host.size() + 255) & ~(size_t)255;
+        host.resize(o + std::max<size_t>(n, 64));
+        return o;
+    }
+    template <typename V>
+    size_t put(const V& v)
+    {
+        const size_t n = v.size() * sizeof(v[0]), o = room(n);
+        if (n) std::memcpy(host.data() + o, v.data(), n);
+        return o;
+    }
+    // allocates b with `more` bytes behind the tables; returns their offset
+    size_t upload(DevBuf& b, size_t more = 0)
+    {
+        const size_t o = (host.size() + 255) & ~(size_t)255;
+        b.ensure(o + more);
+        SYK_HIP(hipMemcpy(b.p, host.data(), host.size(), hipMemcpyHostToDevice));
+        return o;
+    }
+};
+
 int group_tables_key(const ApplyPlan& P, uint32_t esz, int layout)
 {
     return (((int)esz * 2 + P.two_layouts) * 2 + layout) * 256 + P.cut;
@@ -1324,21 +1353,23 @@ const HamiltonianDev::GroupTables& group_tables_for(const HamiltonianDev& H, con
         std::unique_ptr<HamiltonianDev::GroupTables> t(new HamiltonianDev::GroupTables());
         t->n_chunks = (int)G.chunks.size();
         t->n_far = (int)G.far.size();
-        auto up = [](DevBuf& b, const auto& v) {
-            const size_t n = v.size() * sizeof(v[0]);
-            b.ensure(std::max<size_t>(n, 64));
-            if (n) SYK_HIP(hipMemcpy(b.p, v.data(), n, hipMemcpyHostToDevice));
-        };
-        up(t->chunks, G.chunks);
-        up(t->groups, G.groups);
-        up(t->pairs, G.pairs);
         t->n_tables = (int)G.tabs.size();
-        // the QUAD tables in staging order, and the PAIR masks' (once per handle and
-        // element type); finished before this returns, as later calls may come on other streams
-        DevBuf idx;
-        up(idx, G.tabs);
+        // the records, the table indices and (filled on the device) the QUAD tables in staging order
         const uint32_t n16 = (uint32_t)G.tabs.size() * 16u;
-        t->tables.ensure(std::max<size_t>((size_t)n16 * H.n_real * esz, 64));
+        TablePack pk;
+        const size_t o_ch = pk.put(G.chunks), o_gr = pk.put(G.groups), o_pr = pk.put(G.pairs), o_far = pk.put(G.far);
+        const size_t o_idx = pk.put(G.tabs);
+        const size_t o_pc = pk.put(P.cut > 1 ? part_bounds(G.cost, P.cut) : std::vector<uint32_t>());
+        const size_t o_tab = pk.upload(t->buf, std::max<size_t>((size_t)n16 * H.n_real * esz, 64));
+        char* d = static_cast<char*>(t->buf.p);
+        t->chunks = d + o_ch;
+        t->groups = d + o_gr;
+        t->pairs = d + o_pr;
+        t->far = d + o_far;
+        t->part_chunk = d + o_pc;
+        t->tables = d + o_tab;
+        // the PAIR masks' tables once per handle and element type; all finished before
+        // this returns, as later calls may come on other streams
         const dim3 og((n16 + 255) / 256, (uint32_t)H.n_real), pg((uint32_t)H.host_masks->size(), (uint32_t)H.n_real);
         size_t n_pairs = 0;
         for (const MaskRec& m : *H.host_masks) n_pairs += (m.type_tab >> 28) == MASK_PAIR;
@@ -1348,8 +1379,8 @@ const HamiltonianDev::GroupTables& group_tables_for(const HamiltonianDev& H, con
         auto build = [&](auto zero, const auto* tab4) {
             typedef decltype(zero) R;
             if (n16)
-                hipLaunchKernelGGL(k_order_tables<R>, og, dim3(256), 0, 0, tab4, idx.as<uint32_t>(), t->n_tables, H.n_real,
-                                   t->tables.as<cplx<R>>());
+                hipLaunchKernelGGL(k_order_tables<R>, og, dim3(256), 0, 0, tab4, reinterpret_cast<const uint32_t*>(d + o_idx),
+                                   t->n_tables, H.n_real, static_cast<cplx<R>*>(t->tables));
             if (need)
                 hipLaunchKernelGGL(k_pair_tables<R>, pg, dim3(256), 0, 0, H.masks, H.phi2_d, H.w2_d, H.n_real, H.M,
                                    pt.as<cplx<R>>());
@@ -1359,8 +1390,6 @@ const HamiltonianDev::GroupTables& group_tables_for(const HamiltonianDev& H, con
         SYK_HIP(hipGetLastError());
         SYK_HIP(hipStreamSynchronize(0));
         pt.ready = true;
-        up(t->far, G.far);
-        if (P.cut > 1) up(t->part_chunk, part_bounds(G.cost, P.cut));
         it = H.group_tables.emplace(key, std::move(t)).first;
     }
     return *it->second;
@@ -1388,21 +1417,15 @@ const HamiltonianDev::ApplyTables& apply_tables_for(const HamiltonianDev& H, con
         std::unique_ptr<HamiltonianDev::ApplyTables> t(new HamiltonianDev::ApplyTables());
         t->n_chunks = (int)ch.size();
         t->n_far = (int)far.size();
-        if (!ch.empty()) {
-            t->chunks.ensure(ch.size() * sizeof(QApplyChunk));
-            SYK_HIP(hipMemcpy(t->chunks.p, ch.data(), ch.size() * sizeof(QApplyChunk), hipMemcpyHostToDevice));
-        }
-        if (!far.empty()) {
-            t->far.ensure(far.size() * sizeof(FarRec));
-            SYK_HIP(hipMemcpy(t->far.p, far.data(), far.size() * sizeof(FarRec), hipMemcpyHostToDevice));
-        }
-        if (P.cut > 1) {
-            const std::vector<uint32_t> pb = part_bounds(chunk_costs(ch), P.cut);
-            t->part_chunk.ensure(pb.size() * sizeof(uint32_t));
-            SYK_HIP(hipMemcpy(t->part_chunk.p, pb.data(), pb.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-        }
-        t->recs.ensure(rc.size() * sizeof(QRec));
-        SYK_HIP(hipMemcpy(t->recs.p, rc.data(), rc.size() * sizeof(QRec), hipMemcpyHostToDevice));
+        TablePack pk;
+        const size_t o_ch = pk.put(ch), o_rc = pk.put(rc), o_far = pk.put(far);
+        const size_t o_pc = pk.put(P.cut > 1 ? part_bounds(chunk_costs(ch), P.cut) : std::vector<uint32_t>());
+        (void)pk.upload(t->buf);
+        const char* d = static_cast<const char*>(t->buf.p);
+        t->chunks = d + o_ch;
+        t->recs = d + o_rc;
+        t->far = d + o_far;
+        t->part_chunk = d + o_pc;
         it = H.apply_tables.emplace(key, std::move(t)).first;
     }
     return *it->second;
@@ -1786,19 +1809,19 @@ void launch_apply_impl(const HamiltonianDev& H, syk_dtype dtype, int nvec, const
                 const KTerms<R> T{tab4, H.qinfo, phi2, w2, H.diag.as<double>(), H.n_real, M};
                 if (P.groups) {
                     const HamiltonianDev::GroupTables& Tb = group_tables_for(H, P, (uint32_t)esz, layout);
-                    L.far = Tb.far.as<FarRec>();
+                    L.far = static_cast<const FarRec*>(Tb.far);
                     L.n_far = Tb.n_far;
                     L.n_chunks = Tb.n_chunks;
                     L.n_tables = Tb.n_tables;
-                    L.part_chunk = Tb.part_chunk.as<uint32_t>();
+                    L.part_chunk = static_cast<const uint32_t*>(Tb.part_chunk);
                     launch_groups<R>(H, T, Tb, L, ncols, src, dst, pt, s);
                 } else {
                     const HamiltonianDev::ApplyTables& Tb = apply_tables_for(H, P, (uint32_t)esz, layout);
-                    L.far = Tb.far.as<FarRec>();
+                    L.far = static_cast<const FarRec*>(Tb.far);
                     L.n_far = Tb.n_far;
                     L.n_chunks = Tb.n_chunks;
-                    L.part_chunk = Tb.part_chunk.as<uint32_t>();
-                    launch_t<R>(P, T, Tb.chunks.as<QApplyChunk>(), Tb.recs.as<QRec>(), L, ncols, nc, src, dst, pt, s);
+                    L.part_chunk = static_cast<const uint32_t*>(Tb.part_chunk);
+                    launch_t<R>(P, T, static_cast<const QApplyChunk*>(Tb.chunks), static_cast<const QRec*>(Tb.recs), L, ncols, nc, src, dst, pt, s);
                 }
             };
             if (dtype == SYK_C128) launch(0.0, H.tab4_d, H.phi2_d, H.w2_d);

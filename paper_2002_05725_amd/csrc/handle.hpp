@@ -29,13 +29,16 @@ struct HamiltonianDev {
     const std::vector<uint64_t>* bin_off = nullptr;
     // Per-launch-shape chunks and class-sorted records of the apply kernel.
     struct ApplyTables {
-        DevBuf chunks, recs, far, part_chunk;
+        DevBuf buf;   // all of the following
+        const void *chunks = nullptr, *recs = nullptr, *far = nullptr, *part_chunk = nullptr;
         int n_chunks = 0, n_far = 0;
     };
     mutable std::map<int, std::unique_ptr<ApplyTables>> apply_tables;
     // Tables of the 16-row kernel, per element size, layout and split.
     struct GroupTables {
-        DevBuf chunks, groups, tables, pairs, far, part_chunk;
+        DevBuf buf;   // all of the following
+        const void *chunks = nullptr, *groups = nullptr, *pairs = nullptr, *far = nullptr, *part_chunk = nullptr;
+        void* tables = nullptr;
         int n_chunks = 0, n_far = 0, n_tables = 0;
     };
     mutable TableBuf pair_tab_d, pair_tab_f;   // its PAIR tables per element type
